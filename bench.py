@@ -59,7 +59,8 @@ PROFILE_DIR = os.path.join(ROOT, "profiles")
 # what the pass kernel's counters depend on: its code, its launch shape, the
 # pass order the host picks and the compiler flags
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_0904_1179_amd", "csrc", f)
-                  for f in ("kernels.hip", "device.h", "geom.h", "launch.h", "layout.cpp", "api.hip")] + \
+                  for f in ("pass.h", "pass_kernels.h", "pass_f64.hip", "pass_f32.hip", "kernels.hip", "device.h",
+                            "geom.h", "launch.h", "layout.cpp", "api.hip")] + \
                  [os.path.join(ROOT, "paper_0904_1179_amd", "build.py")]
 
 
@@ -541,7 +542,7 @@ def main():
     traffic = stored_traffic(f"k_update_{L}x4_fp{prec}_traffic.txt")
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": f"k_update<mu, {'double' if prec == 64 else 'float'}>",
+                "kernel": f"k_pass_split<mu, {'double' if prec == 64 else 'float'}>",
                 "algorithmic_bytes_per_update": bytes_per_update(prec), "algorithmic_bytes_per_launch": alg_bytes,
                 "stored_bytes_per_update": stored_bytes_per_update(prec), "stored_bytes_per_launch": stored_bytes,
                 "achieved_stored_gbs": round(stored_bytes / pass_s / 1e9, 1),

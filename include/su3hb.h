@@ -235,15 +235,13 @@ su3_status su3_gauge_transform(su3_ctx *c, uint64_t gseed);
 su3_status su3_profile(su3_ctx *c, int32_t enable);
 su3_status su3_profile_read(su3_ctx *c, double *total_ms, uint64_t *passes);
 
-/* Lanes per link of the heat-bath passes.  By default (lanes = 0) a pass of
- * more than 32768 links runs one lane per link; smaller passes, which would
- * leave most of the GPU idle and take about one link update's latency, run 2
- * (up to 32768 links) or 4 (up to 8192) lanes per link that share the
- * staple directions and the random draws of the update (1-hit only).  The
- * result does not depend on the choice: every variant adds in the same order
- * and gives the same bits.  lanes = 1, 2 or 4 forces that count (2 and 4 need
- * nhit = 1, else SU3_EINVAL).  su3_get_lanes_per_link returns the count the
- * passes use. */
+/* Lanes per link of the heat-bath passes: a setting from when small passes
+ * shared the work of one link between 2 or 4 lanes.  Every pass now runs three
+ * waves per 64 links, one per staple direction, at any size; the setting has no
+ * effect on it and none on the results.  lanes = 0 (the default) lets
+ * su3_get_lanes_per_link report 4 (1-hit passes of up to 8192 links), 2 (up to
+ * 32768) or 1; lanes = 1, 2 or 4 is reported back (2 and 4 need nhit = 1, else
+ * SU3_EINVAL). */
 su3_status su3_set_lanes_per_link(su3_ctx *c, int32_t lanes);
 su3_status su3_get_lanes_per_link(su3_ctx *c, int32_t *lanes);
 
@@ -266,9 +264,7 @@ su3_status su3_stream_copy(void *dst, const void *src, size_t bytes, void *hip_s
  * checkerboard pass -- and retires
  * the jobs that reached their sweep count (final plaquette and heat-bath
  * counters kept, memory freed); su3_server_run does the same for several
- * sweeps per call.  A group of 1-hit jobs with at most 32768 links per pass
- * in total runs two lanes per link (such a pass is bound by the latency of
- * one update).  A job's links get the same per-link
+ * sweeps per call.  A job's links get the same per-link
  * arithmetic and the same keyed random numbers as a single lattice run with
  * su3_start/su3_sweep, so its result is the same alone and in the mix.
  * su3_server_step synchronises the server's stream.

@@ -161,7 +161,17 @@ namespace {
 // nu < mu, in meas[(mu - 1) * nlat * meas_blocks .. mu * nlat * meas_blocks).
 su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nullptr, const double *betas = nullptr)
 {
-    const int lanes = lanes_per_link(c->g, c->p.nhit, c->lanes_requested);
+    PassArgs a;
+    a.links = c->links;
+    a.g = c->g;
+    a.beta0 = betas ? betas[0] : beta;
+    a.beta1 = betas ? betas[1] : beta;
+    a.twob = betas != nullptr;
+    a.big = pass_big(c->g, c->p.precision);
+    a.seed = c->p.seed;
+    a.nhit = c->p.nhit;
+    a.counters = counters_of(c);
+    a.stream = c->stream;
     for (int32_t s = 0; s < n; ++s) {
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par) {
@@ -177,19 +187,12 @@ su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nul
                     hipError_t e = hipEventRecord(c->ev[c->ev_used], c->stream);
                     if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
                 }
+                a.mu = mu;
+                a.par = par;
+                a.sweep = c->sweep_index;
                 const bool measured = meas && s == n - 1 && mu >= 1 && par == 1;
-                hipError_t e;
-                if (betas)
-                    e = su3hb::launch_update_twob(c->p.precision, c->links, c->g, mu, par, betas[0], betas[1],
-                                                  c->sweep_index, c->p.seed, c->p.nhit, counters_of(c), c->stream);
-                else if (measured)
-                    e = su3hb::launch_update_measured(
-                        c->p.precision, c->links, c->g, mu, beta, c->sweep_index, c->p.seed, c->p.nhit, lanes,
-                        counters_of(c), meas + (size_t)(mu - 1) * c->g.nlat * su3hb::meas_blocks(c->g, lanes),
-                        c->stream);
-                else
-                    e = su3hb::launch_update(c->p.precision, c->links, c->g, mu, par, beta, c->sweep_index, c->p.seed,
-                                             c->p.nhit, lanes, counters_of(c), c->stream);
+                a.meas = measured ? meas + (size_t)(mu - 1) * c->g.nlat * su3hb::meas_blocks(c->g) : nullptr;
+                hipError_t e = launch_pass(c->p.precision, a);
                 if (e != hipSuccess) return hip_fail(e, "update kernel");
                 if (timed) {
                     e = hipEventRecord(c->ev[c->ev_used + 1], c->stream);
@@ -282,8 +285,7 @@ su3_status su3_sweep_measure(su3_ctx *c, int32_t n, double beta, double *out, si
             double *meas = (double *)(c->scratch + meas_offset(c->g));
             st = enqueue_sweeps(c, 1, beta, meas);
             if (st != SU3_OK) return st;
-            e = launch_measure_final(meas, c->g, lanes_per_link(c->g, c->p.nhit, c->lanes_requested),
-                                     slots + 4 * k, c->stream);
+            e = launch_measure_final(meas, c->g, slots + 4 * k, c->stream);
             if (e != hipSuccess) return hip_fail(e, "plaquette kernels");
         }
         hipError_t e = hipMemcpyAsync(h.data(), slots, sizeof(double) * 4 * m, hipMemcpyDeviceToHost, c->stream);

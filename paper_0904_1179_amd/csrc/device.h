@@ -117,104 +117,113 @@ template <typename R> __device__ __forceinline__ R retrace(const M3<R> &A)
     return A.e[0][0].re + A.e[1][1].re + A.e[2][2].re;
 }
 
-// precision-generic device math (FP32 tier: single-precision functions)
 // ---------------------------------------------------------------------------
 // FP64 elementary functions on the argument ranges of the heat bath.  The
 // general library versions handle every input (signs, infinities, huge
 // arguments) and cost 70-100 instructions each; the heat bath only takes
-// logarithms of uniforms in (0, 1] and sines/cosines of pi t with t in [0, 2].
-// Both below are short series with exact coefficients, accurate to about an
-// ulp over those ranges.
+// logarithms of uniforms in (0, 1] and sines/cosines of 2 pi u.  The passes
+// issue one vector instruction per 4 cycles at best, whatever it is, so the
+// count is what matters: polynomials of the lowest degree whose error stays
+// below 2^-56 (Chebyshev interpolation of the series, coefficients rounded to
+// FP64), range reduction on the integer the uniform is made of, and one
+// hardware reciprocal with a cubic correction instead of a division.
 // ---------------------------------------------------------------------------
 
+// n / d for |n| < d, d in [1.7, 2.5]: the hardware reciprocal r0 (2^-24), e =
+// 1 - d r0, r = r0 (1 + e + e^2) up to e^3, and one residual correction of n r.
+// The general division's scaling and special cases cannot occur here.
+__device__ __forceinline__ double div_mid(double n, double d)
+{
+    const double r0 = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, r0, 1.0);
+    const double r = fma(r0, fma(e, e, e), r0);
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
 // ln x for 0 < x <= 1 (normal numbers): x = 2^k m with m in [1/sqrt 2, sqrt 2),
-// ln m = 2 atanh(s) = 2 (s + s^3/3 + s^5/5 + ...) with s = (m - 1)/(m + 1),
-// |s| <= 0.1716; ten terms leave a truncation below 1e-17 relative.  ln 2 is
-// split into a 40-bit head (k * head is exact) and the rounded remainder.
-__host__ __device__ inline double log_unit(double x)
+// ln m = 2 atanh(s) = 2 s (1 + z p(z)) with s = (m - 1)/(m + 1), z = s^2 <=
+// 0.0295 and p(z) = 1/3 + z/5 + ... to 5e-18 relative to ln m.  ln 2 is split
+// into a 40-bit head (k * head is exact) and the rounded remainder.
+__device__ __forceinline__ double log_unit(double x)
 {
     constexpr double kLn2Hi = 0x1.62e42fefa2000p-1;
     constexpr double kLn2Lo = 0x1.9ef35793c7673p-41;
     constexpr double kSqrtHalf = 0x1.6a09e667f3bcdp-1;
     int k;
     double m = frexp(x, &k);  // m in [1/2, 1)
-    if (m < kSqrtHalf) {
-        m += m;
-        --k;
-    }
-    const double s = (m - 1.0) / (m + 1.0);
+    const bool low = m < kSqrtHalf;
+    m = low ? m + m : m;
+    k = low ? k - 1 : k;
+    const double s = div_mid(m - 1.0, m + 1.0);
     const double z = s * s;
-    double p = 1.0 / 19.0;
-    p = fma(p, z, 1.0 / 17.0);
-    p = fma(p, z, 1.0 / 15.0);
-    p = fma(p, z, 1.0 / 13.0);
-    p = fma(p, z, 1.0 / 11.0);
-    p = fma(p, z, 1.0 / 9.0);
-    p = fma(p, z, 1.0 / 7.0);
-    p = fma(p, z, 1.0 / 5.0);
-    p = fma(p, z, 1.0 / 3.0);
+    double p = 0.07308250539378183;
+    p = fma(p, z, 0.0766585841296273);
+    p = fma(p, z, 0.0909144464614301);
+    p = fma(p, z, 0.11111105566041697);
+    p = fma(p, z, 0.14285714312997824);
+    p = fma(p, z, 0.19999999999949725);
+    p = fma(p, z, 0.3333333333333335);
     const double s2 = s + s;
     const double lnm = fma(s2 * z, p, s2);  // 2 s (1 + z p)
     const double dk = (double)k;
     return fma(dk, kLn2Hi, fma(dk, kLn2Lo, lnm));
 }
 
-// sin(pi r), cos(pi r) for |r| <= 1/4 from their Taylor series in y = r^2:
-// coefficients (-1)^j pi^(2j+1)/(2j+1)! (sine, j = 0..8) and
-// (-1)^j pi^(2j)/(2j)! (cosine, j = 0..9); the first omitted terms are below
-// 1e-17 at |pi r| = pi/4.
-__host__ __device__ inline void sincospi_quarter(double r, double *sn, double *cs)
+// The angle 2 pi u of the uniform u = (h + 1/2) 2^-32: 4 u = q + r with q the
+// nearest integer and |r| < 1/2.  r comes from the low 30 bits of h as a
+// signed number, q (mod 4) from h + 2^29: no rounding anywhere.
+__device__ __forceinline__ int quarter_low(uint32_t h) { return (int)(h << 2) >> 2; }  // 2^30 r - 1/2
+__device__ __forceinline__ uint32_t quarter_turns(uint32_t h) { return (h + 0x20000000u) >> 30; }
+
+// sin and cos of 2 pi u = pi/2 (q + r): with t = r/2, |t| <= 1/4, polynomials
+// in t^2 for sin(pi t) and cos(pi t) (to 4e-17 and 2e-17), then the quadrant.
+__device__ __forceinline__ void sincos_2pi_u32(uint32_t h, double *sn, double *cs)
 {
-    const double y = r * r;
-    double ps = 7.952054001475513e-07;
-    ps = fma(ps, y, -2.1915353447830217e-05);
-    ps = fma(ps, y, 0.00046630280576761255);
-    ps = fma(ps, y, -0.0073704309457143504);
-    ps = fma(ps, y, 0.08214588661112823);
-    ps = fma(ps, y, -0.5992645293207921);
-    ps = fma(ps, y, 2.5501640398773455);
-    ps = fma(ps, y, -5.16771278004997);
+    const double t = fma((double)quarter_low(h), 0x1p-31, 0x1p-32);
+    const double y = t * t;
+    double ps = 0.0004622109894019862;
+    ps = fma(ps, y, -0.007370143626152033);
+    ps = fma(ps, y, 0.08214587730556389);
+    ps = fma(ps, y, -0.5992645291845261);
+    ps = fma(ps, y, 2.5501640398766154);
+    ps = fma(ps, y, -5.167712780049969);
     ps = fma(ps, y, 3.141592653589793);
-    double pc = -1.3878952462213771e-07;
-    pc = fma(pc, y, 4.303069587032947e-06);
-    pc = fma(pc, y, -0.0001046381049248457);
-    pc = fma(pc, y, 0.0019295743094039231);
-    pc = fma(pc, y, -0.02580689139001406);
-    pc = fma(pc, y, 0.2353306303588932);
-    pc = fma(pc, y, -1.3352627688545895);
-    pc = fma(pc, y, 4.0587121264167685);
+    double pc = -0.00010373975549425398;
+    pc = fma(pc, y, 0.001929501537233591);
+    pc = fma(pc, y, -0.025806888533614774);
+    pc = fma(pc, y, 0.23533063030363824);
+    pc = fma(pc, y, -1.3352627688541205);
+    pc = fma(pc, y, 4.058712126416767);
     pc = fma(pc, y, -4.934802200544679);
-    *sn = r * ps;
-    *cs = fma(pc, y, 1.0);
+    const double s = t * ps, c = fma(pc, y, 1.0);
+    const uint32_t q = quarter_turns(h);
+    const double ss = (q & 1) ? c : s, cc = (q & 1) ? s : c;
+    *sn = (q & 2) ? -ss : ss;
+    *cs = ((q + 1) & 2) ? -cc : cc;
 }
 
-// t in [0, 2]: q = nearest integer to 2t, r = t - q/2 (exact, |r| <= 1/4),
-// pi t = pi r + q pi/2.
-__host__ __device__ inline void sincospi_0to2(double t, double *sn, double *cs)
+// cos^2(2 pi u) = 1/2 + cos(4 pi u)/2 = 1/2 + (-1)^q cos(pi r)/2: one
+// polynomial in r^2 <= 1/4 (to 2e-17) instead of a sine and a cosine.
+__device__ __forceinline__ double cos2_2pi_u32(uint32_t h)
 {
-    const double q = rint(t + t);
-    const double r = fma(q, -0.5, t);
-    double s, c;
-    sincospi_quarter(r, &s, &c);
-    const int iq = (int)q & 3;
-    const double ss = (iq & 1) ? c : s, cc = (iq & 1) ? s : c;
-    *sn = (iq & 2) ? -ss : ss;
-    *cs = (iq == 1 || iq == 2) ? -cc : cc;
+    const double r = fma((double)quarter_low(h), 0x1p-30, 0x1p-31);
+    const double w = r * r;
+    double p = 4.166464350419119e-06;
+    p = fma(p, w, -0.00010458293377269001);
+    p = fma(p, w, 0.001929562682292385);
+    p = fma(p, w, -0.025806890032216145);
+    p = fma(p, w, 0.23533063027286294);
+    p = fma(p, w, -1.3352627688519192);
+    p = fma(p, w, 4.0587121264167365);
+    p = fma(p, w, -4.934802200544679);
+    const double half = fma(0.5 * w, p, 0.5);
+    return 0.5 + ((quarter_turns(h) & 1) ? -half : half);
 }
 
-// cos^2(pi t) for t in [0, 2]: only the parity of the quadrant matters.
-__host__ __device__ inline double cospi_sq_0to2(double t)
-{
-    const double q = rint(t + t);
-    const double r = fma(q, -0.5, t);
-    double s, c;
-    sincospi_quarter(r, &s, &c);
-    return ((int)q & 1) ? s * s : c * c;
-}
-
-// FP32 versions for the FP32 tier: the same reduction, Taylor series cut where
-// the first omitted term is below 3e-9 at |pi r| = pi/4 (sine j = 0..4,
-// cosine j = 0..5), coefficients as above rounded to float.
+// FP32 tier: t in [0, 2], q = nearest integer to 2t, r = t - q/2 (exact, |r| <=
+// 1/4), pi t = pi r + q pi/2; Taylor series in r^2 cut where the first omitted
+// term is below 3e-9 at |pi r| = pi/4 (sine j = 0..4, cosine j = 0..5).
 __host__ __device__ inline void sincospi_quarter(float r, float *sn, float *cs)
 {
     const float y = r * r;
@@ -251,22 +260,36 @@ __host__ __device__ inline float cospi_sq_0to2(float t)
     return ((int)q & 1) ? s * s : c * c;
 }
 
-// Precision-generic helpers of the heat bath (arguments: uniforms in (0, 1]
-// and t in [0, 2]): the functions above; FP32 logarithm from the library.
-__device__ __forceinline__ double log_r(double x) { return log_unit(x); }
-__device__ __forceinline__ float log_r(float x) { return logf(x); }
-// 1/sqrt(x) and sqrt(x) for x > 0.  FP64: the library reciprocal square root
-// (the hardware estimate plus one correction step, ~11 instructions, about an
-// ulp) instead of a correctly rounded square root (~22) and a division (~11);
-// FP32: the plain float operations.
-__device__ __forceinline__ double rsqrt_r(double x) { return rsqrt(x); }
-__device__ __forceinline__ float rsqrt_r(float x) { return 1.0f / sqrtf(x); }
-__device__ __forceinline__ double sqrt_pos_r(double x) { return x * rsqrt(x); }
+// 1/sqrt(x) and sqrt(x) for x > 0 (normal numbers).  FP64: the hardware
+// estimate y (2^-23) with one third-order correction, y + y e (1/2 + 3 e/8),
+// e = 1 - x y^2, about an ulp; a correctly rounded square root and division
+// take three times the instructions.
+__device__ __forceinline__ double rsqrt_r(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+__device__ __forceinline__ double sqrt_pos_r(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double s = x * y;
+    const double e = fma(-s, y, 1.0);
+    return fma(s * e, fma(e, 0.375, 0.5), s);
+}
+// FP32: correctly rounded square root and reciprocal.  The reciprocal is the
+// general division's own refinement without its scaling, which only acts on
+// operands near the ends of the exponent range; s is the root of a float, so
+// it lies in [2^-75, 2^64].
+__device__ __forceinline__ float rsqrt_r(float x)
+{
+    const float s = sqrtf(x);
+    float r = __builtin_amdgcn_rcpf(s);
+    r = fmaf(fmaf(-s, r, 1.0f), r, r);
+    float q = fmaf(fmaf(-s, r, 1.0f), r, r);
+    return fmaf(fmaf(-s, q, 1.0f), r, q);
+}
 __device__ __forceinline__ float sqrt_pos_r(float x) { return sqrtf(x); }
-__device__ __forceinline__ double cospi_sq_r(double t) { return cospi_sq_0to2(t); }
-__device__ __forceinline__ float cospi_sq_r(float t) { return cospi_sq_0to2(t); }
-__device__ __forceinline__ void sincospi_r(double t, double *s, double *c) { sincospi_0to2(t, s, c); }
-__device__ __forceinline__ void sincospi_r(float t, float *s, float *c) { sincospi_0to2(t, s, c); }
 
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror & Shaw, SC'11)
@@ -275,50 +298,104 @@ struct U64x4 {
     uint64_t w[4];
 };
 
+// y + x in one instruction.  The compiler would zero-extend x into a register
+// pair first (two moves) and add the pairs; the 32 x 32 + 64 bit multiply-add
+// takes x as it is, with a factor of one, at the same issue cost as a move.
+__device__ __forceinline__ uint64_t add_u32(uint64_t y, uint32_t x)
+{
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, 1, %2" : "=v"(r) : "v"(x), "v"(y) : "vcc");
+    return r;
+}
+
+// a ^ b ^ c, both halves with the three-input bit operation
+__device__ __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c)
+{
+    const uint32_t lo = __builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, 0x96);
+    const uint32_t hi =
+        __builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32), (uint32_t)(c >> 32), 0x96);
+    return (uint64_t)hi << 32 | lo;
+}
+
 // Full 128-bit product a m, m a compile-time constant, from 32-bit limbs
 // a = a1 2^32 + a0, m = m1 2^32 + m0:
 //   t = a0 m1 + hi(a0 m0),  u = a1 m0 + lo(t),
 //   a m = lo(a0 m0) + 2^32 lo(u) + 2^64 (a1 m1 + hi(t) + hi(u)),
-// where no partial sum overflows 64 bits.  Four 32x32+64 multiply-adds; the
-// separate low product and high product would form the cross terms twice.
+// where no partial sum overflows 64 bits.  Eight multiply-adds and nothing
+// else (13 instructions with zero-extended addends).
 template <uint64_t M> __device__ __forceinline__ void mulhilo64(uint64_t a, uint64_t &lo, uint64_t &hi)
 {
     constexpr uint32_t m0 = (uint32_t)M, m1 = (uint32_t)(M >> 32);
     const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
     const uint64_t p = (uint64_t)a0 * m0;
-    const uint64_t t = (uint64_t)a0 * m1 + (p >> 32);
-    const uint64_t u = (uint64_t)a1 * m0 + (uint32_t)t;
+    const uint64_t t = add_u32((uint64_t)a0 * m1, (uint32_t)(p >> 32));
+    const uint64_t u = add_u32((uint64_t)a1 * m0, (uint32_t)t);
     lo = (u << 32) | (uint32_t)p;
-    hi = (uint64_t)a1 * m1 + ((t >> 32) + (u >> 32));
+    hi = add_u32(add_u32((uint64_t)a1 * m1, (uint32_t)(t >> 32)), (uint32_t)(u >> 32));
+}
+// the same for a < 2^32
+template <uint64_t M> __device__ __forceinline__ void mulhilo32(uint32_t a, uint64_t &lo, uint32_t &hi)
+{
+    constexpr uint32_t m0 = (uint32_t)M, m1 = (uint32_t)(M >> 32);
+    const uint64_t p = (uint64_t)a * m0;
+    const uint64_t t = add_u32((uint64_t)a * m1, (uint32_t)(p >> 32));
+    lo = (t << 32) | (uint32_t)p;
+    hi = (uint32_t)(t >> 32);
+}
+
+constexpr uint64_t kPhiloxMul0 = 0xD2E7470EE14C6C93ull, kPhiloxMul1 = 0xCA5A826395121157ull;
+constexpr uint64_t kPhiloxBump0 = 0x9E3779B97F4A7C15ull, kPhiloxBump1 = 0xBB67AE8584CAA73Bull;
+
+// rounds FIRST..9 on the counter c with the key of round FIRST
+template <int FIRST> __device__ __forceinline__ U64x4 philox_rounds(U64x4 c, uint64_t k0, uint64_t k1)
+{
+#pragma unroll
+    for (int round = FIRST; round < 10; ++round) {
+        uint64_t lo_a, hi_a, lo_b, hi_b;
+        mulhilo64<kPhiloxMul0>(c.w[0], lo_a, hi_a);
+        mulhilo64<kPhiloxMul1>(c.w[2], lo_b, hi_b);
+        c = U64x4{{xor3(hi_b, c.w[1], k0), lo_b, xor3(hi_a, c.w[3], k1), lo_a}};
+        k0 += kPhiloxBump0;
+        k1 += kPhiloxBump1;
+    }
+    return c;
 }
 
 __device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
                                                uint64_t k1)
 {
-    constexpr uint64_t kMul0 = 0xD2E7470EE14C6C93ull, kMul1 = 0xCA5A826395121157ull;
-    constexpr uint64_t kBump0 = 0x9E3779B97F4A7C15ull, kBump1 = 0xBB67AE8584CAA73Bull;
-#pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        uint64_t lo_a, hi_a, lo_b, hi_b;
-        mulhilo64<kMul0>(c0, lo_a, hi_a);
-        mulhilo64<kMul1>(c2, lo_b, hi_b);
-        c0 = hi_b ^ c1 ^ k0;
-        c1 = lo_b;
-        c2 = hi_a ^ c3 ^ k1;
-        c3 = lo_a;
-        k0 += kBump0;
-        k1 += kBump1;
-    }
-    return U64x4{{c0, c1, c2, c3}};
+    return philox_rounds<0>(U64x4{{c0, c1, c2, c3}}, k0, k1);
+}
+
+// Philox4x64-10 of the heat bath: counter (lid, sweep, ctr, 0), key (seed, 0),
+// with lid < 2^32 the only word that differs between the lanes of a wave.  In
+// the first two rounds half of the state is then uniform (scalar products) and
+// the other half has a 32-bit factor.
+__device__ __forceinline__ U64x4 philox_link(uint32_t lid, uint64_t sweep, uint64_t ctr, uint64_t seed)
+{
+    uint64_t lo_a, lo_b;
+    uint32_t hi_a, hi_b;
+    mulhilo32<kPhiloxMul0>(lid, lo_a, hi_a);
+    const uint64_t c0 = __umul64hi(ctr, kPhiloxMul1) ^ sweep ^ seed, c1 = ctr * kPhiloxMul1;  // uniform
+    // round 1: state (c0, c1, hi_a, lo_a)
+    mulhilo32<kPhiloxMul1>(hi_a, lo_b, hi_b);
+    const uint64_t k0 = seed + kPhiloxBump0, k1 = kPhiloxBump1;
+    const U64x4 c{{(uint64_t)hi_b ^ (c1 ^ k0), lo_b, lo_a ^ (__umul64hi(c0, kPhiloxMul0) ^ k1), c0 * kPhiloxMul0}};
+    return philox_rounds<2>(c, k0 + kPhiloxBump0, k1 + kPhiloxBump1);
 }
 
 // Purpose tags (counter word 3).
 enum : uint64_t { kTagHeatbath = 0, kTagHot = 1, kTagGauge = 2 };
 
-// (k + 1/2) * 2^-52 from the top 52 bits: exact in FP64, never 0 or 1.
-__device__ __forceinline__ double unif52(uint64_t w) { return (double(w >> 12) + 0.5) * 0x1p-52; }
+// (k + 1/2) * 2^-52 from the top 52 bits k: exact in FP64, never 0 or 1.  The
+// bits become the mantissa of 1 + k 2^-52, and subtracting 1 - 2^-53 is exact.
+__device__ __forceinline__ double unif52(uint64_t w)
+{
+    const uint64_t one_k = (w >> 12) | 0x3ff0000000000000ull;
+    return __longlong_as_double((long long)one_k) - 0x1.fffffffffffffp-1;
+}
 // (h + 1/2) * 2^-32 from a 32-bit half: exact in FP64, never 0 or 1.
-__device__ __forceinline__ double unif32(uint32_t h) { return (double(h) + 0.5) * 0x1p-32; }
+__device__ __forceinline__ double unif32(uint32_t h) { return fma((double)h, 0x1p-32, 0x1p-33); }
 
 // ---------------------------------------------------------------------------
 // XCD-aware workgroup order.  MI355X deals workgroups round-robin to its 8
@@ -457,8 +534,7 @@ template <typename R> __device__ __forceinline__ store_t<R> *link_at(store_t<R> 
     return block + (size_t)(n >> 4) * (kEntries * kTile) + (n & (kTile - 1));
 }
 
-// row 2 = conj(row 0 x row 1): the third row of an SU(3) matrix, computed
-// exactly as reunit() computes it
+// row 2 = conj(row 0 x row 1): the third row of an SU(3) matrix
 template <typename R> __device__ __forceinline__ void rebuild_row2(M3<R> &u)
 {
 #pragma unroll
@@ -466,6 +542,19 @@ template <typename R> __device__ __forceinline__ void rebuild_row2(M3<R> &u)
         const int a = (k + 1) % 3, b = (k + 2) % 3;
         const Cx<R> p = cmul(u.e[0][a], u.e[1][b]), q = cmul(u.e[0][b], u.e[1][a]);
         u.e[2][k] = Cx<R>{p.re - q.re, -(p.im - q.im)};
+    }
+}
+
+// FP64: each real entry a sum of four products in one chain of fused
+// multiply-adds (24 instructions instead of 30, and fewer roundings)
+__device__ __forceinline__ void rebuild_row2(M3<double> &u)
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const Cx<double> a = u.e[0][(k + 1) % 3], b = u.e[1][(k + 2) % 3];
+        const Cx<double> c = u.e[0][(k + 2) % 3], d = u.e[1][(k + 1) % 3];
+        u.e[2][k].re = fma(c.im, d.im, fma(-c.re, d.re, fma(-a.im, b.im, a.re * b.re)));
+        u.e[2][k].im = fma(c.im, d.re, fma(c.re, d.im, fma(-a.im, b.re, -(a.re * b.im))));
     }
 }
 
@@ -544,55 +633,6 @@ template <typename R> __device__ __forceinline__ M3<R> load_link12(const store_t
     return m;
 }
 
-template <typename R>
-__device__ __forceinline__ void load_link12_pair(M3<R> &p, const store_t<R> *bp, int np, M3<R> &q,
-                                                 const store_t<R> *bq, int nq)
-{
-    const store_t<R> *pp = link_at<R>(bp, np), *pq = link_at<R>(bq, nq);
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const store_t<R> vp = pp[e * kTile];
-        const store_t<R> vq = pq[e * kTile];
-        p.e[e / 3][e % 3] = Cx<R>{vp.x, vp.y};
-        q.e[e / 3][e % 3] = Cx<R>{vq.x, vq.y};
-    }
-    rebuild_row2(p);
-    rebuild_row2(q);
-}
-
-// Nontemporal access to the link a pass updates: no other thread of the pass
-// reads it, so it should not displace reusable staple links from L2.
-template <typename R> struct NtVec;
-template <> struct NtVec<double> { typedef double type __attribute__((ext_vector_type(2))); };
-template <> struct NtVec<float> { typedef float type __attribute__((ext_vector_type(2))); };
-
-template <typename R> __device__ __forceinline__ M3<R> load_link12_nt(const store_t<R> *block, int n)
-{
-    typedef typename NtVec<R>::type V;
-    M3<R> m;
-    const V *p = reinterpret_cast<const V *>(link_at<R>(block, n));
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const V v = __builtin_nontemporal_load(p + e * kTile);
-        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
-    }
-    rebuild_row2(m);
-    return m;
-}
-
-template <typename R> __device__ __forceinline__ void store_link_nt(store_t<R> *block, int n, const M3<R> &m)
-{
-    typedef typename NtVec<R>::type V;
-    V *p = reinterpret_cast<V *>(link_at<R>(block, n));
-#pragma unroll
-    for (int e = 0; e < kEntries; ++e) {
-        V v;
-        v.x = m.e[e / 3][e % 3].re;
-        v.y = m.e[e / 3][e % 3].im;
-        __builtin_nontemporal_store(v, p + e * kTile);
-    }
-}
-
 // Stores rows 0 and 1 of m (row 2 is implied).
 template <typename R> __device__ __forceinline__ void store_link(store_t<R> *block, int n, const M3<R> &m)
 {
@@ -620,31 +660,35 @@ template <typename To, typename From> __device__ __forceinline__ M3<To> convert(
 // row 2 = conj(row0 x row1).
 __device__ __forceinline__ void reunit(M3<double> &u)
 {
-    Cx<double> *r0 = u.e[0], *r1 = u.e[1], *r2 = u.e[2];
-    const double i0 = rsqrt(r0[0].re * r0[0].re + r0[0].im * r0[0].im + r0[1].re * r0[1].re + r0[1].im * r0[1].im +
-                            r0[2].re * r0[2].re + r0[2].im * r0[2].im);
+    Cx<double> *r0 = u.e[0], *r1 = u.e[1];
+    double n0 = r0[0].re * r0[0].re;
+    n0 = fma(r0[0].im, r0[0].im, n0);
+#pragma unroll
+    for (int k = 1; k < 3; ++k) n0 = fma(r0[k].im, r0[k].im, fma(r0[k].re, r0[k].re, n0));
+    const double i0 = rsqrt_r(n0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         r0[k].re *= i0;
         r0[k].im *= i0;
     }
-    Cx<double> d{0.0, 0.0};
+    Cx<double> d = cmul_cn(r0[0], r1[0]);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) d = cmadd_cn(d, r0[k], r1[k]);
+    for (int k = 1; k < 3; ++k) d = cmadd_cn(d, r0[k], r1[k]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        r1[k].re -= d.re * r0[k].re - d.im * r0[k].im;
-        r1[k].im -= d.re * r0[k].im + d.im * r0[k].re;
+        r1[k].re = fma(d.im, r0[k].im, fma(-d.re, r0[k].re, r1[k].re));
+        r1[k].im = fma(-d.im, r0[k].re, fma(-d.re, r0[k].im, r1[k].im));
     }
-    const double i1 = rsqrt(r1[0].re * r1[0].re + r1[0].im * r1[0].im + r1[1].re * r1[1].re + r1[1].im * r1[1].im +
-                            r1[2].re * r1[2].re + r1[2].im * r1[2].im);
+    double n1 = r1[0].re * r1[0].re;
+    n1 = fma(r1[0].im, r1[0].im, n1);
+#pragma unroll
+    for (int k = 1; k < 3; ++k) n1 = fma(r1[k].im, r1[k].im, fma(r1[k].re, r1[k].re, n1));
+    const double i1 = rsqrt_r(n1);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         r1[k].re *= i1;
         r1[k].im *= i1;
     }
-    // r2_k = conj(r0_{k+1} r1_{k+2} - r0_{k+2} r1_{k+1})
-    (void)r2;
     rebuild_row2(u);
 }
 

@@ -34,34 +34,30 @@ constexpr size_t kOffSums = 16 * (size_t)kCounterSlots;
 constexpr size_t kOffMeasure = kOffSums + 256;
 constexpr size_t kOffPartials = kOffMeasure + 32 * (size_t)kMeasureChunk;
 
-// Unsigned division by a divisor fixed for a launch (Granlund and Montgomery,
-// "Division by invariant integers using multiplication", 1994): with
-// l = ceil(log2 d), m = floor(2^32 (2^l - d) / d) + 1, s1 = min(l, 1),
-// s2 = max(l - 1, 0) and t = floor(m x / 2^32),
-//   floor(x / d) = (t + ((x - t) >> s1)) >> s2   for every 0 <= x < 2^32,
-// a multiply-high and three shifts/adds instead of a division sequence.
+// Division of 0 <= x < 2^31 by a divisor fixed for a launch (the multiplier
+// method of Granlund and Montgomery, "Division by invariant integers using
+// multiplication", 1994): with l = ceil(log2 d) and m = ceil(2^(31 + l) / d),
+//   floor(x / d) = floor(2 x m / 2^32) >> l.
+// m d exceeds 2^(31 + l) by less than d <= 2^l, and x < 2^31 times that stays
+// below 2^(31 + l), so the quotient is exact; m <= 2^32 - 1 because
+// d > 2^(l - 1).  A shift, a multiply-high and a shift.
 struct FastDiv {
-    uint32_t d, m, s1, s2;
+    uint32_t d, m, l;
 };
 
 inline FastDiv make_fastdiv(uint32_t d)
 {
     uint32_t l = 0;
     while ((1ull << l) < d) ++l;
-    FastDiv f;
-    f.d = d;
-    f.m = (uint32_t)((((uint64_t)1 << 32) * ((1ull << l) - d)) / d + 1);
-    f.s1 = l < 1 ? l : 1;
-    f.s2 = l > 1 ? l - 1 : 0;
-    return f;
+    const uint64_t top = 1ull << (31 + l);
+    return FastDiv{d, (uint32_t)((top + d - 1) / d), l};
 }
 
 // constexpr: usable in host and device code alike
 constexpr int div_by(int x, const FastDiv &f)
 {
     const uint32_t ux = (uint32_t)x;
-    const uint32_t t = (uint32_t)(((uint64_t)f.m * ux) >> 32);
-    return (int)((t + ((ux - t) >> f.s1)) >> f.s2);
+    return (int)((uint32_t)(((uint64_t)f.m * (ux + ux)) >> 32) >> f.l);
 }
 
 // Sites are addressed by (layer, parity, i): i = lex >> 1 with

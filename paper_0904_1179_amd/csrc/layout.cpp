@@ -113,14 +113,8 @@ size_t link_bytes_of(const su3_params *p, const Geom &g)
     return (size_t)8 * kEntries * (size_t)g.stride * (p->precision == 64 ? 16u : 8u);
 }
 
-// Passes of at most kLanes4Max links run with 4 lanes per link, of at most
-// kLanes2Max with 2, larger ones with 1.  Measured per pass (FP64): 2048 links
-// 11.3 us with 1 lane, 9.3 us with 4; 32768 links about even (FP32: 13.5 vs
-// 11 us with 2); 65536 links (2 x 16^4) 19 us with 1 lane, 21 us with 2, whose
-// two waves per SIMD then issue 1.6 times the instructions of one.  Per sweep,
-// 4 against 2 lanes: 2048 to 5000 links (8^4, 2 x 8^4, 10^4) 76-80 against
-// 83-85 us in FP64, even in FP32; 10368 links (12^4) 91 against 86 us in FP64,
-// 85 against 76 us in FP32.
+// Every pass runs three waves per 64 links whatever this count; it stays a
+// setting of the interface.
 constexpr long long kLanes4Max = 8192, kLanes2Max = 32768;
 
 int lanes_per_link(const Geom &g, int nhit, int requested)
@@ -131,11 +125,12 @@ int lanes_per_link(const Geom &g, int nhit, int requested)
     return n <= kLanes4Max ? 4 : (n <= kLanes2Max ? 2 : 1);
 }
 
-int pass_links_per_block(const Geom &g, int lanes)
+bool pass_big(const Geom &g, int precision)
 {
-    if (lanes > 1) return kBlock / lanes;
-    return g.nlat == 1 ? kPassBlock : kBlock;
+    return (unsigned long long)g.stride * kEntries * (precision == 64 ? 16u : 8u) >= (1ull << 32);
 }
+
+int pass_links_per_block(const Geom &, int) { return kPassBlock; }
 
 int pass_blocks(const Geom &g, int nb) { return (int)ceil_div((long long)g.nlat * g.Vh, nb); }
 
@@ -171,10 +166,6 @@ int plaq_walk_blocks(const Geom &g, int nch)
 
 int meas_blocks(const Geom &g, int lanes) { return pass_blocks(g, pass_links_per_block(g, lanes)); }
 
-// the most workgroups a measured pass can have: 64 links per workgroup
-// (one lane per link on a single torus, or 4 lanes per link)
-static int meas_blocks_max(const Geom &g) { return pass_blocks(g, 64); }
-
 int polyakov_blocks(const Geom &g) { return (int)ceil_div((long long)g.L[0] * g.L[1] * g.L[2], kBlock); }
 
 // plaquette partials: per layer and workgroup the plaquette sum, then the
@@ -184,7 +175,7 @@ size_t meas_offset(const Geom &g) { return (size_t)round_up(kOffPartials + 2 * 8
 // measured-pass partials: 3 passes x nlat doubles per workgroup
 size_t polyakov_offset(const Geom &g)
 {
-    return (size_t)round_up((long long)meas_offset(g) + 3 * 8LL * g.nlat * meas_blocks_max(g), 256);
+    return (size_t)round_up((long long)meas_offset(g) + 3 * 8LL * g.nlat * meas_blocks(g), 256);
 }
 
 size_t scratch_bytes_of(const Geom &g)

@@ -27,11 +27,13 @@ size_t link_bytes_of(const su3_params *p, const Geom &g);
 // ~1e-7 from the rounding of FP64-reunitarised rows.
 inline double unitarity_tol(int precision) { return precision == 64 ? 1e-10 : 1e-5; }
 
-// Lanes per link of a pass: 1, or 2 or 4 for passes too small to fill the
-// GPU with one lane per link (1-hit only).  `requested` = 0 picks by the
-// number of links per pass; 1, 2, 4 force that count (2, 4 need nhit = 1).
+// The count that su3_get_lanes_per_link reports: `requested` if 1, 2 or 4, and
+// for 0 one by the number of links per pass.  The passes do not depend on it.
 int lanes_per_link(const Geom &g, int nhit, int requested);
-// Links per workgroup of a pass with `lanes` lanes per link.
+// Whether a (direction, parity) block reaches 4 GiB, so that link offsets need
+// 64 bits.
+bool pass_big(const Geom &g, int precision);
+// Links per workgroup of a pass (64, whatever the lanes).
 int pass_links_per_block(const Geom &g, int lanes);
 // workgroups covering the nlat * Vh links of one pass, nb links each
 int pass_blocks(const Geom &g, int nb);
@@ -43,8 +45,8 @@ int plaq_blocks(const Geom &g);
 int plaq_walk_chunks(const Geom &g, int precision);
 // workgroups per layer of the plaquette walk with nch chunks (<= plaq_blocks)
 int plaq_walk_blocks(const Geom &g, int nch);
-// workgroups of a measured pass of su3_sweep_measure with `lanes` lanes per link
-int meas_blocks(const Geom &g, int lanes);
+// workgroups of a measured pass of su3_sweep_measure
+int meas_blocks(const Geom &g, int lanes = 1);
 // Polyakov loops: workgroups per layer
 int polyakov_blocks(const Geom &g);
 

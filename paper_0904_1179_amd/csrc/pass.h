@@ -1,0 +1,520 @@
+// pass.h -- device code of one heat-bath pass: addressing, staples, random
+// draws and the Cabibbo-Marinari heat bath.  Shared by the single-lattice and
+// the batched kernels of pass.hip.
+//
+// What bounds a pass.  A SIMD issues one vector instruction per 4 cycles, FP64,
+// FP32 and 64-bit integer alike (moves and bit operations in half of that when
+// four waves share it), and one wave alone only one per 8 cycles.  An update
+// is about 3000 vector instructions for 864 (FP64) or 432 (FP32) bytes, so a
+// pass needs at least two, better three or four waves per SIMD that are ready
+// to issue, and every instruction counts.
+#pragma once
+
+#include "launch.h"
+
+namespace su3hb {
+namespace {
+
+// ---------------------------------------------------------------------------
+// Addresses.  A link's byte offset in its block is a 32-bit number, added to a
+// scalar base by the load itself, as long as a block has less than 4 GiB
+// (pass_big); larger lattices take 64-bit offsets (BIG).
+// ---------------------------------------------------------------------------
+template <bool BIG> struct OffsetOf {
+    using type = uint32_t;
+};
+template <> struct OffsetOf<true> {
+    using type = uint64_t;
+};
+template <bool BIG> using offset_t = typename OffsetOf<BIG>::type;
+
+template <typename R, bool BIG> __device__ __forceinline__ offset_t<BIG> link_offset(int n)
+{
+    constexpr uint32_t E = sizeof(store_t<R>);
+    const uint32_t u = (uint32_t)n, in_tile = u & (kTile - 1);
+    if constexpr (BIG)
+        return (uint64_t)(u >> 4) * (kEntries * kTile * E) + in_tile * E;
+    else
+        return u * (kEntries * E) - in_tile * ((kEntries - 1) * E);
+}
+
+// One (direction, parity) block of links.
+template <typename R> struct Block {
+    const char *base;
+};
+template <typename R> __device__ __forceinline__ Block<R> block_of(const store_t<R> *links, const Geom &g, int dir, int par)
+{
+    return Block<R>{(const char *)(links + (size_t)(dir * 2 + par) * (size_t)g.stride * kEntries)};
+}
+
+// Rows 0 and 1 of the link at offset o (row 2 is left undefined).
+template <typename R, typename O> __device__ __forceinline__ void load_rows(M3<R> &m, Block<R> b, O o)
+{
+    const store_t<R> *p = (const store_t<R> *)(b.base + o);
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) {
+        const store_t<R> v = p[e * kTile];
+        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
+    }
+}
+// Rows 0 and 1 of two links, entry by entry in turn: the two are the same
+// link for two neighbouring sites, so the second use finds the line in cache.
+template <typename R, typename O>
+__device__ __forceinline__ void load_rows_pair(M3<R> &m, Block<R> bm, O om, M3<R> &n, Block<R> bn, O on)
+{
+    const store_t<R> *p = (const store_t<R> *)(bm.base + om), *q = (const store_t<R> *)(bn.base + on);
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) {
+        const store_t<R> v = p[e * kTile], w = q[e * kTile];
+        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
+        n.e[e / 3][e % 3] = Cx<R>{w.x, w.y};
+    }
+}
+
+// Nontemporal access to the link a pass updates: no other thread of the pass
+// reads it, so it should not displace reusable staple links from L2.
+template <typename R> struct NtVec;
+template <> struct NtVec<double> { typedef double type __attribute__((ext_vector_type(2))); };
+template <> struct NtVec<float> { typedef float type __attribute__((ext_vector_type(2))); };
+
+template <typename R, typename O> __device__ __forceinline__ void load_own(M3<R> &m, Block<R> b, O o)
+{
+    typedef typename NtVec<R>::type V;
+    const V *p = (const V *)(b.base + o);
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) {
+        const V v = __builtin_nontemporal_load(p + e * kTile);
+        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
+    }
+}
+// FP64: nontemporal store (a plain one: -3 % at 32^4); FP32, which is not
+// bound by memory: a plain store (+1 %).
+template <typename R, typename O> __device__ __forceinline__ void store_own(Block<R> b, O o, const M3<R> &m)
+{
+    typedef typename NtVec<R>::type V;
+    V *p = (V *)(b.base + o);
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) {
+        V v;
+        v.x = m.e[e / 3][e % 3].re;
+        v.y = m.e[e / 3][e % 3].im;
+        if constexpr (sizeof(R) == 8)
+            __builtin_nontemporal_store(v, p + e * kTile);
+        else
+            p[e * kTile] = v;
+    }
+}
+
+// The site of a link: coordinates, half-index and layer.
+struct Site {
+    int x[4];
+    int i;      // half-index within the layer
+    int layer;  // 0 on a single torus
+};
+
+// The site at pass-order position v (order_site), v < nlat * Vh.
+template <bool DLT> __device__ __forceinline__ Site site_of(const Geom &g, int par, int v)
+{
+    Site s;
+    s.layer = DLT && v >= g.Vh ? 1 : 0;
+    s.i = order_site(g, par, DLT ? v - s.layer * g.Vh : v, s.x);
+    return s;
+}
+
+// What one step along a direction adds to the half-index, and the layer bit it
+// flips.  Along directions 1..3 a step moves lex by an even number, so the
+// half-index moves by the same amount whatever the other coordinates; along
+// direction 0 it depends on x0 alone.  So steps along two directions add up.
+struct Step {
+    int di;
+    int flip;
+};
+template <int D, int S> __device__ __forceinline__ Step step_of(const Geom &g, const Site &s)
+{
+    const int h = g.L[0] >> 1;
+    Step r;
+    bool edge;
+    if constexpr (D == 0) {
+        const bool odd = s.x[0] & 1;
+        if constexpr (S > 0) {
+            edge = s.x[0] == g.L[0] - 1;
+            r.di = edge ? 1 - h : (odd ? 1 : 0);
+        } else {
+            edge = s.x[0] == 0;
+            r.di = edge ? h - 1 : (odd ? 0 : -1);
+        }
+    } else {
+        const int hs = D == 1 ? h : D == 2 ? h * g.L[1] : h * g.L[1] * g.L[2];
+        const int wrap = (g.L[D] - 1) * hs;
+        if constexpr (S > 0) {
+            edge = s.x[D] == g.L[D] - 1;
+            r.di = edge ? -wrap : hs;
+        } else {
+            edge = s.x[D] == 0;
+            r.di = edge ? wrap : -hs;
+        }
+    }
+    r.flip = edge ? (int)((g.flip >> D) & 1u) : 0;
+    return r;
+}
+
+// Plane element of the site after the steps a (and b).
+template <bool DLT> __device__ __forceinline__ int elem(const Geom &g, const Site &s, Step a)
+{
+    const int i = s.i + a.di;
+    return DLT ? i + ((s.layer ^ a.flip) ? g.Vh : 0) : i;
+}
+template <bool DLT> __device__ __forceinline__ int elem(const Geom &g, const Site &s, Step a, Step b)
+{
+    const int i = s.i + a.di + b.di;
+    return DLT ? i + ((s.layer ^ a.flip ^ b.flip) ? g.Vh : 0) : i;
+}
+
+// The two steps along a direction known at run time (uniform over the wave).
+template <int MU> __device__ __forceinline__ void steps_of(const Geom &g, const Site &s, int nu, Step &up, Step &dn)
+{
+    if (MU != 0 && nu == 0) {
+        up = step_of<0, +1>(g, s);
+        dn = step_of<0, -1>(g, s);
+    } else if (MU != 1 && nu == 1) {
+        up = step_of<1, +1>(g, s);
+        dn = step_of<1, -1>(g, s);
+    } else if (MU != 2 && nu == 2) {
+        up = step_of<2, +1>(g, s);
+        dn = step_of<2, -1>(g, s);
+    } else {
+        up = step_of<3, +1>(g, s);
+        dn = step_of<3, -1>(g, s);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Staple of U_MU(x): A = sum over nu != MU (ascending) of D_nu,
+//   D_nu = up_nu + dn_nu,
+//   up_nu = U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+ = a (c b)^+,
+//   dn_nu = U_nu(x+mu-nu)^+ U_mu(x-nu)^+ U_nu(x-nu) = (e d)^+ f,
+// with a = U_nu(x+mu), b = U_mu(x+nu), c = U_nu(x), d = U_nu(x+mu-nu),
+// e = U_mu(x-nu), f = U_nu(x-nu).  up_nu is the plaquette based at x, dn_nu
+// the one based at x - nu.
+//
+// Rounding order, fixed for every kernel: c b, e d and a (c b)^+ are SU(3)
+// products (rows 0 and 1 formed, row 2 rebuilt).  FP64: D_nu = up_nu, and the
+// products of (e d)^+ f are added to it one fused multiply-add at a time (no
+// separate sum).  FP32: dn_nu is formed entry by entry from zero, then D_nu =
+// up_nu + dn_nu.  A = (D_0 + D_1) + D_2 over the three directions in
+// increasing order.  All kernels add in exactly this order, so a lattice gets
+// the same bits from each of them.
+// ---------------------------------------------------------------------------
+
+// (ed^+ f)_rc
+template <typename R> __device__ __forceinline__ Cx<R> dn_entry(const M3<R> &ed, const M3<R> &f, int r, int c)
+{
+    Cx<R> dn = cmul_cn(ed.e[0][r], f.e[0][c]);
+    dn = cmadd_cn(dn, ed.e[1][r], f.e[1][c]);
+    return cmadd_cn(dn, ed.e[2][r], f.e[2][c]);
+}
+
+// D = up, then D += (e d)^+ f.  CROSS: also cross = (e d)^+ f where `crosses`
+// (the lower plaquette's base site lies in the other layer of a double-layered
+// torus), else 0; in FP64 as the difference that the sum made.
+template <typename R, bool CROSS>
+__device__ __forceinline__ void add_dn(M3<R> &D, const M3<R> &ed, const M3<R> &f, M3<R> &cross, bool crosses)
+{
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const Cx<R> up = D.e[r][c];
+            if constexpr (sizeof(R) == 8) {
+                Cx<R> t = cmadd_cn(up, ed.e[0][r], f.e[0][c]);
+                t = cmadd_cn(t, ed.e[1][r], f.e[1][c]);
+                D.e[r][c] = cmadd_cn(t, ed.e[2][r], f.e[2][c]);
+                if constexpr (CROSS) {
+                    cross.e[r][c].re = crosses ? D.e[r][c].re - up.re : R(0);
+                    cross.e[r][c].im = crosses ? D.e[r][c].im - up.im : R(0);
+                }
+            } else {
+                const Cx<R> dn = dn_entry(ed, f, r, c);
+                D.e[r][c].re = up.re + dn.re;
+                D.e[r][c].im = up.im + dn.im;
+                if constexpr (CROSS) {
+                    cross.e[r][c].re = crosses ? dn.re : R(0);
+                    cross.e[r][c].im = crosses ? dn.im : R(0);
+                }
+            }
+        }
+}
+
+// Offsets of the six links of direction nu's two staples.
+template <bool BIG> struct StapleAt {
+    offset_t<BIG> here, mu, up, dn, mu_dn;  // x, x + mu, x + nu, x - nu, x + mu - nu
+    bool crosses;                           // x - nu lies in the other layer
+    int dn_layer;
+};
+template <int MU, typename R, bool DLT, bool BIG>
+__device__ __forceinline__ StapleAt<BIG> staple_at(const Geom &g, const Site &s, Step mu, Step up, Step dn)
+{
+    StapleAt<BIG> a;
+    a.here = link_offset<R, BIG>(DLT ? s.i + (s.layer ? g.Vh : 0) : s.i);
+    a.mu = link_offset<R, BIG>(elem<DLT>(g, s, mu));
+    a.up = link_offset<R, BIG>(elem<DLT>(g, s, up));
+    a.dn = link_offset<R, BIG>(elem<DLT>(g, s, dn));
+    a.mu_dn = link_offset<R, BIG>(elem<DLT>(g, s, mu, dn));
+    a.crosses = DLT && dn.flip;
+    a.dn_layer = DLT ? s.layer ^ dn.flip : 0;
+    return a;
+}
+
+// The two staples of direction nu.  TWOB: FP64 D = w[layer] up + w[base layer
+// of the lower plaquette] dn; FP32 D = up and cross = dn, to be weighted where
+// they are added.
+template <int MU, typename R, bool CROSS, bool TWOB, bool BIG>
+__device__ __forceinline__ void staple_nu(M3<R> &D, M3<R> &cross, const store_t<R> *links, const Geom &g, int par, int nu,
+                                          const StapleAt<BIG> &at, int layer, R w0, R w1)
+{
+    const int opp = par ^ 1;
+    const Block<R> umu = block_of<R>(links, g, MU, opp), unu_par = block_of<R>(links, g, nu, par),
+                   unu_opp = block_of<R>(links, g, nu, opp);
+    M3<R> b, e, c, d, a, f;
+    load_rows_pair(b, umu, at.up, e, umu, at.dn);
+    load_rows_pair(c, unu_par, at.here, d, unu_par, at.mu_dn);
+    load_rows_pair(a, unu_opp, at.mu, f, unu_opp, at.dn);
+    rebuild_row2(b);
+    rebuild_row2(d);
+    const M3<R> cb = mul_nn_su3(c, b);
+    const M3<R> ed = mul_nn_su3(e, d);
+    D = mul_nd_su3(a, cb);
+    rebuild_row2(f);
+    if constexpr (TWOB && sizeof(R) == 4) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) cross.e[r][k] = dn_entry(ed, f, r, k);
+    } else if constexpr (TWOB) {
+        const R wu = layer ? w1 : w0, wd = at.dn_layer ? w1 : w0;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const Cx<R> dn = dn_entry(ed, f, r, k);
+                D.e[r][k].re = D.e[r][k].re * wu + wd * dn.re;
+                D.e[r][k].im = D.e[r][k].im * wu + wd * dn.im;
+            }
+    } else {
+        add_dn<R, CROSS>(D, ed, f, cross, at.crosses);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Cabibbo-Marinari heat bath of one link in staple A.  W = U A; for subgroup
+// (i,j): v = 1/2 (Re(w_ii + w_jj), -Im(w_ij + w_ji), Re(w_ji - w_ij),
+// Im(w_jj - w_ii)), k = |v|, alpha = 2 beta k / 3.  Kennedy-Pendleton attempt t
+// uses Philox block (lid, sweep, sub<<32 | t, heat-bath tag):
+//   lambda^2 = -(ln u1 + cos^2(2 pi u2) ln u3) / (2 alpha), accept iff u4^2 <= 1 - lambda^2,
+//   a0 = 1 - 2 lambda^2, cos(theta) = 2 u5 - 1, phi = 2 pi u6;
+// then rows i, j of U and W are multiplied from the left by r = P(a) P(v/k)
+// with P(p) = [[p0 + i p3, p2 + i p1], [-p2 + i p1, p0 - i p3]].
+// The SU(2) step runs in the link precision R (FP64 links: FP64 throughout,
+// accept decisions in FP64); the uniforms are formed exactly in FP64 first.
+// The link is reunitarised in FP64 at the end.
+// ---------------------------------------------------------------------------
+
+// What an attempt needs from its random numbers, independent of the link:
+// q = ln u1 + cos^2(2 pi u2) ln u3 (so lambda^2 = -q / (2 alpha)), u4^2,
+// cos(theta), sin(theta) cos(phi), sin(theta) sin(phi).
+template <typename R> struct KPDraw {
+    R q, u4sq, cth, sc, ss;
+};
+
+template <typename R> __device__ __forceinline__ KPDraw<R> kp_draw(uint32_t lid, uint64_t sweep, uint64_t seed, int sub, int t)
+{
+    const U64x4 w = philox_link(lid, sweep, ((uint64_t)sub << 32) | (uint64_t)t, seed);
+    const uint32_t h2 = (uint32_t)w.w[2], h4 = (uint32_t)(w.w[2] >> 32);
+    const uint32_t h5 = (uint32_t)w.w[3], h6 = (uint32_t)(w.w[3] >> 32);
+    const R u1 = R(unif52(w.w[0])), u3 = R(unif52(w.w[1]));
+    const R u4 = R(unif32(h4)), u5 = R(unif32(h5));
+    KPDraw<R> d;
+    d.u4sq = u4 * u4;
+    d.cth = R(2) * u5 - R(1);
+    // FP64: |cth| < 1 (u5 is never 0 or 1), so the argument is positive
+    const R sth = sqrt_pos_r(R(1) - d.cth * d.cth);
+    R sph, cph, c2;
+    if constexpr (sizeof(R) == 8) {
+        c2 = cos2_2pi_u32(h2);
+        d.q = log_unit(u1) + c2 * log_unit(u3);
+        sincos_2pi_u32(h6, &sph, &cph);
+    } else {
+        c2 = cospi_sq_0to2(R(2) * R(unif32(h2)));
+        d.q = logf(u1) + c2 * logf(u3);
+        sincospi_0to2(R(2) * R(unif32(h6)), &sph, &cph);
+    }
+    d.sc = sth * cph;
+    d.ss = sth * sph;
+    return d;
+}
+
+// A draw of attempt 0 in LDS, slot-major over the 64 lanes.
+template <typename R> __device__ __forceinline__ void draw_put(store_t<R> (*buf)[64], int lane, const KPDraw<R> &d)
+{
+    store_t<R> a, b, c;
+    a.x = d.q;
+    a.y = d.u4sq;
+    b.x = d.cth;
+    b.y = d.sc;
+    c.x = d.ss;
+    c.y = R(0);
+    buf[0][lane] = a;
+    buf[1][lane] = b;
+    buf[2][lane] = c;
+}
+template <typename R> __device__ __forceinline__ KPDraw<R> draw_get(const store_t<R> (*buf)[64], int lane)
+{
+    const store_t<R> a = buf[0][lane], b = buf[1][lane];
+    return KPDraw<R>{a.x, a.y, b.x, b.y, buf[2][lane].x};
+}
+
+// Attempts and acceptances of a wave, uniform over it.
+struct Counts {
+    uint32_t att, acc;
+};
+__device__ __forceinline__ uint32_t lanes_of(bool p) { return (uint32_t)__popcll(__ballot(p)); }
+
+// The heat bath proper.  first(sub): the draw of attempt 0.  q32 = 3/(2 beta).
+// All 64 lanes take part; only the `active` ones count.  There is no branch
+// per lane: a rejected attempt (3 % of them, so nearly every wave has one)
+// rotates by the identity, which leaves finite rows as they are.  Returns
+// Re Tr W after the last subgroup, i.e. Re Tr(U_new A) before the final
+// reunitarisation.  Projections are of 2 v; the factor is exact and cancels.
+template <typename R, bool HIT1, typename First>
+__device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint32_t lid, uint64_t sweep, uint64_t seed,
+                                           int nhit, bool active, Counts &n, First first)
+{
+    M3<R> W = mul_nn(U, A);
+#pragma unroll
+    for (int sub = 0; sub < 3; ++sub) {
+        const int i = (sub == 1) ? 1 : 0;
+        const int j = (sub == 0) ? 1 : 2;
+        const R v0 = W.e[i][i].re + W.e[j][j].re;
+        const R v1 = -(W.e[i][j].im + W.e[j][i].im);
+        const R v2 = W.e[j][i].re - W.e[i][j].re;
+        const R v3 = W.e[j][j].im - W.e[i][i].im;
+        const R k2 = v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+        // a staple projection that vanishes exactly: nothing to sample, no attempt
+        bool todo = k2 != R(0);
+        const R rk = rsqrt_r(k2);
+        const R inv2alpha = q32 * rk;
+        bool ok = false;
+        R a0 = R(1), a1 = R(0), a2 = R(0), a3 = R(0);
+        auto attempt = [&](const KPDraw<R> &d) {
+            const R lam2 = -d.q * inv2alpha;
+            const bool hit = todo && d.u4sq <= R(1) - lam2;
+            n.att += lanes_of(todo && active);
+            n.acc += lanes_of(hit && active);
+            const R b0 = R(1) - R(2) * lam2;
+            const R rho2 = R(1) - b0 * b0;
+            const R rho = rho2 > R(0) ? sqrt_pos_r(rho2) : R(0);
+            a0 = hit ? b0 : a0;
+            a1 = hit ? rho * d.sc : a1;
+            a2 = hit ? rho * d.ss : a2;
+            a3 = hit ? rho * d.cth : a3;
+            ok = ok || hit;
+            todo = todo && !hit;
+        };
+        attempt(first(sub));
+        if constexpr (!HIT1)
+            for (int t = 1; t < nhit && __ballot(todo) != 0; ++t) attempt(kp_draw<R>(lid, sweep, seed, sub, t));
+        const R b0 = v0 * rk, b1 = v1 * rk, b2 = v2 * rk, b3 = v3 * rk;
+        // quaternion product c = a * b  <=>  P(c) = P(a) P(b)
+        const R p0 = a0 * b0 - a1 * b1 - a2 * b2 - a3 * b3;
+        const R p1 = a0 * b1 + b0 * a1 - (a2 * b3 - a3 * b2);
+        const R p2 = a0 * b2 + b0 * a2 - (a3 * b1 - a1 * b3);
+        const R p3 = a0 * b3 + b0 * a3 - (a1 * b2 - a2 * b1);
+        const R c0 = ok ? p0 : R(1), c1 = ok ? p1 : R(0), c2 = ok ? p2 : R(0), c3 = ok ? p3 : R(0);
+        const Cx<R> r00{c0, c3}, r01{c2, c1}, r10{-c2, c1}, r11{c0, -c3};
+#pragma unroll
+        for (int col = 0; col < 3; ++col) {
+            const Cx<R> ui = U.e[i][col], uj = U.e[j][col];
+            U.e[i][col] = cmadd(cmul(r00, ui), r01, uj);
+            U.e[j][col] = cmadd(cmul(r10, ui), r11, uj);
+            const Cx<R> wi = W.e[i][col], wj = W.e[j][col];
+            W.e[i][col] = cmadd(cmul(r00, wi), r01, wj);
+            W.e[j][col] = cmadd(cmul(r10, wi), r11, wj);
+        }
+    }
+    M3<double> Ud = convert<double>(U);
+    reunit(Ud);
+    U = convert<R>(Ud);
+    return double(W.e[0][0].re) + double(W.e[1][1].re) + double(W.e[2][2].re);
+}
+
+// Re Tr(u s), accumulated in FP64.
+template <typename R> __device__ __forceinline__ double retr_mul(const M3<R> &u, const M3<R> &s)
+{
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            t += (double)u.e[i][k].re * (double)s.e[k][i].re - (double)u.e[i][k].im * (double)s.e[k][i].im;
+    return t;
+}
+
+// Sum over the wave, in a fixed order.
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+
+// A wave's counts go to counter slot `slot`, so that few concurrent
+// workgroups update the same address.
+__device__ __forceinline__ void add_counts(Counts n, unsigned long long *__restrict__ counters, int slot, int lane)
+{
+    if (lane == 0 && n.att != 0) {
+        unsigned long long *c = counters + 2 * slot;
+        atomicAdd(&c[0], (unsigned long long)n.att);
+        atomicAdd(&c[1], (unsigned long long)n.acc);
+    }
+}
+
+// Tile of this workgroup in a pass of parity `par`.  Every pass reads the
+// whole lattice, and the passes of a sweep alternate in parity, so the odd
+// passes walk the tiles backwards: a pass begins on the links its
+// predecessor read last, which are still in L2 and in the memory-side cache.
+// The order does not change the result, only which links are in cache.
+__device__ __forceinline__ int pass_tile(int par)
+{
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    return par ? (int)gridDim.x - 1 - t : t;
+}
+
+// The staple directions nu != MU in increasing order.
+template <int MU> constexpr int kNu0 = MU == 0 ? 1 : 0;
+template <int MU> constexpr int kNu1 = MU <= 1 ? 2 : 1;
+template <int MU> constexpr int kNu2 = MU <= 2 ? 3 : 2;
+
+// A matrix in LDS, entry-major over the 64 lanes.
+template <typename R, int N> __device__ __forceinline__ void lds_put(store_t<R> (*buf)[64], int lane, const M3<R> &m)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        store_t<R> v;
+        v.x = m.e[e / 3][e % 3].re;
+        v.y = m.e[e / 3][e % 3].im;
+        buf[e][lane] = v;
+    }
+}
+template <typename R, int N> __device__ __forceinline__ M3<R> lds_get(const store_t<R> (*buf)[64], int lane)
+{
+    M3<R> m;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const store_t<R> v = buf[e][lane];
+        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
+    }
+    return m;
+}
+
+}  // namespace
+}  // namespace su3hb

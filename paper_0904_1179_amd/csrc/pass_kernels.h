@@ -1,0 +1,282 @@
+// pass_kernels.h -- the kernels of a heat-bath pass, for one lattice and for a
+// batch of them, and their launch.  Instantiated per link precision
+// (pass_f64.hip, pass_f32.hip).
+#pragma once
+
+#include "pass.h"
+
+namespace su3hb {
+namespace {
+
+constexpr int kSplitBlock = 192;  // threads per workgroup of the split pass: three waves for 64 links
+
+// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed
+// and 128 taken by the unmeasured passes, so four waves share a SIMD.  Asked
+// for four, the compiler schedules for registers and the pass is 10 % slower;
+// held to exactly three waves it is 3 % slower.
+template <typename R> constexpr int kSplitWaves = sizeof(R) == 8 ? 3 : 5;
+
+// FP32 with per-layer couplings keeps the six staple terms apart (D: the two
+// of a direction one after the other).
+template <typename R, bool TWOB> constexpr bool kTermsApart = TWOB && sizeof(R) == 4;
+
+template <typename R, bool TWOB> struct SplitLds {
+    store_t<R> D[2][kTermsApart<R, TWOB> ? 18 : 9][64];  // D of the first two directions
+    store_t<R> draw[2][3][64];                           // draws of subgroups 0 and 1
+};
+
+// One tile of 64 links with three waves: wave w forms the two staples of one
+// direction and the random draw of one subgroup for all 64 links, and wave 0
+// then adds the three and runs the heat bath.
+//
+// One lane per link, all in one thread, takes 3900 instructions (FP64) and 220
+// registers: two waves per SIMD, each of which spends a third of its time on
+// memory while the other alone issues at half rate.  Here no wave has more
+// than one direction in registers (128 in FP64, 75 in FP32), the six loads of
+// U_mu(x +- nu) that all directions share are in flight together, the chain
+// from the first load to the store is 1560 instructions instead of 3900, and
+// nothing is computed twice but the addresses: 3340 instructions per 64 links
+// in all.  Time per pass, one lane per link (up to 8192 links four, up to
+// 32768 two) -> three waves:
+//   FP64  8^4 9.5 -> 6.7, 16^4 13.1 -> 10.1, 2 x 16^4 18.2 -> 16.2, 24^4 35.4 ->
+//         31.2, 32^4 96.6 -> 88.5, 64^4 1604 -> 1563 us;
+//   FP32  16^4 10.9 -> 8.8, 2 x 16^4 14.0 -> 12.1, 24^4 22.0 -> 19.9, 32^4 50.2 ->
+//         48.7 us, 64^4 865 us either way.
+// What bounds it now: 32^4 FP64 moves 500 MB past L2 at 5.7 TB/s with the
+// vector unit 54 % busy; FP32 keeps it 86 % busy; 8^4 has an eighth of a wave
+// per SIMD and takes the chain's latency.
+template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG>
+__device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const Geom &g, int par, int tile, R q32, R w0,
+                                           R w1, uint64_t sweep, uint64_t seed, int nhit,
+                                           unsigned long long *__restrict__ counters, int slot,
+                                           double *__restrict__ meas, SplitLds<R, TWOB> &lds)
+{
+    static_assert(!MEAS || (MU > 0 && !TWOB), "measured passes: MU = 1, 2, 3 with one coupling");
+    constexpr bool CROSS = MEAS && DLT;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int nlinks = g.nlat * g.Vh;
+    int v = tile * 64 + lane;
+    const bool active = v < nlinks;
+    v = active ? v : nlinks - 1;  // a lane past the end works on the last link and stores nothing
+    const Site s = site_of<DLT>(g, par, v);
+    const int nu = w == 0 ? kNu2<MU> : w == 1 ? kNu0<MU> : kNu1<MU>;
+    const int sub = w == 0 ? 2 : w - 1;
+    Step up, dn;
+    steps_of<MU>(g, s, nu, up, dn);
+    const StapleAt<BIG> at = staple_at<MU, R, DLT, BIG>(g, s, step_of<MU, +1>(g, s), up, dn);
+    const uint32_t lid = 4u * (uint32_t)(s.layer * 2 * g.Vh + 2 * s.i + (s.x[0] & 1)) + MU;
+    // D: the direction's sum; X: its part whose base lies in the other layer
+    // (CROSS), or the lower term (kTermsApart; D is then the upper one)
+    M3<R> D, X;
+    staple_nu<MU, R, CROSS, TWOB, BIG>(D, X, links, g, par, nu, at, s.layer, w0, w1);
+    const KPDraw<R> mine = kp_draw<R>(lid, sweep, seed, sub, 0);
+    if (w != 0) {
+        lds_put<R, 9>(lds.D[w - 1], lane, D);
+        if constexpr (kTermsApart<R, TWOB>) lds_put<R, 9>(lds.D[w - 1] + 9, lane, X);
+        draw_put<R>(lds.draw[w - 1], lane, mine);
+    }
+    const Block<R> own = block_of<R>(links, g, MU, par);
+    M3<R> U;
+    if (w == 0) load_own(U, own, at.here);
+    __syncthreads();
+    double tr = 0.0, trx = 0.0;
+    if (w == 0) {
+        M3<R> A;
+        if constexpr (kTermsApart<R, TWOB>) {
+            // each term weighted and added in turn
+            const R wu = s.layer ? w1 : w0;
+            auto lower = [&](Step d) { return (s.layer ^ d.flip) ? w1 : w0; };
+            set_zero(A);
+            scale_acc(A, lds_get<R, 9>(lds.D[0], lane), wu);
+            scale_acc(A, lds_get<R, 9>(lds.D[0] + 9, lane), lower(step_of<kNu0<MU>, -1>(g, s)));
+            scale_acc(A, lds_get<R, 9>(lds.D[1], lane), wu);
+            scale_acc(A, lds_get<R, 9>(lds.D[1] + 9, lane), lower(step_of<kNu1<MU>, -1>(g, s)));
+            scale_acc(A, D, wu);
+            scale_acc(A, X, lower(dn));
+        } else {
+            A = lds_get<R, 9>(lds.D[0], lane);
+            add_to(A, lds_get<R, 9>(lds.D[1], lane));
+            add_to(A, D);
+        }
+        rebuild_row2(U);
+        Counts n{0, 0};
+        tr = heatbath<R, HIT1>(U, A, q32, lid, sweep, seed, nhit, active, n,
+                               [&](int k) { return k < 2 ? draw_get<R>(lds.draw[k], lane) : mine; });
+        if (active) store_own(own, at.here, U);
+        add_counts(n, counters, slot, lane);
+        if constexpr (MEAS) {
+            // S = sum of D_nu over nu < MU
+            if constexpr (MU == 1) tr = retr_mul(U, lds_get<R, 9>(lds.D[0], lane));
+            if constexpr (MU == 2) {
+                M3<R> S = lds_get<R, 9>(lds.D[0], lane);
+                add_to(S, lds_get<R, 9>(lds.D[1], lane));
+                tr = retr_mul(U, S);
+            }
+            if constexpr (!CROSS) {
+                tr = wave_sum(active ? tr : 0.0);
+                if (lane == 0) meas[0] = tr;
+            }
+        }
+    }
+    if constexpr (CROSS) {
+        // the lower terms whose base lies in the other layer: each wave sums
+        // its own direction's share Re Tr(U_new X)
+        __shared__ double part[3][2];
+        __syncthreads();  // wave 0 has read D
+        if (w == 0) lds_put<R, 9>(lds.D[0], lane, U);
+        __syncthreads();
+        if (nu < MU) trx = retr_mul(lds_get<R, 9>(lds.D[0], lane), X);
+        const bool l1 = s.layer != 0;
+        const double s0 = wave_sum(active ? (l1 ? trx : tr - trx) : 0.0);
+        const double s1 = wave_sum(active ? (l1 ? tr - trx : trx) : 0.0);
+        if (lane == 0) {
+            part[w][0] = s0;
+            part[w][1] = s1;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            meas[0] = part[0][0] + part[1][0] + part[2][0];
+            if (g.nlat == 2) meas[1] = part[0][1] + part[1][1] + part[2][1];
+        }
+    }
+}
+
+template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG>
+__global__ __launch_bounds__(kSplitBlock, kSplitWaves<R>) void k_pass_split(
+    store_t<R> *__restrict__ links, const Geom g, const int par, const R q32, const R w0, const R w1,
+    const uint64_t sweep, const uint64_t seed, const int nhit, unsigned long long *__restrict__ counters,
+    double *__restrict__ meas)
+{
+    __shared__ SplitLds<R, TWOB> lds;
+    pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG>(links, g, par, pass_tile(par), q32, w0, w1, sweep, seed, nhit,
+                                                  counters, blockIdx.x % kCounterSlots,
+                                                  MEAS ? meas + (size_t)g.nlat * blockIdx.x : nullptr, lds);
+}
+
+// The job of tile t: the last one whose tile_begin is at most t.  The lanes of
+// a wave look at 64 jobs at once.
+__device__ __forceinline__ int job_of_tile(const BatchJob *__restrict__ jobs, int njobs, int t)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = njobs;
+    while (n > 1) {
+        const int stride = (n + 63) / 64, k = lane * stride;
+        const int c = (int)lanes_of(k < n && jobs[lo + (k < n ? k : 0)].tile_begin <= t);  // job lo always counts
+        lo += (c - 1) * stride;
+        n = min(stride, n - (c - 1) * stride);
+        if (stride == 1) break;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Batched pass: one launch updates the links U_MU of parity `par` of every
+// job in `jobs` (sorted by tile_begin).  The grid has one workgroup per tile
+// of 64 links of the batch; logical tile t (pass_tile: each XCD works on
+// contiguous stretches of each job's tiles) belongs to the job whose tile range
+// holds t; job j is at sweep index sweep0 + (step - admit_step).  The record
+// of the job is uniform over the workgroup.
+template <int MU, typename R, bool HIT1, bool DLT, bool BIG>
+__global__ __launch_bounds__(kSplitBlock, kSplitWaves<R>) void k_batch_split(const BatchJob *__restrict__ jobs,
+                                                                             const int njobs, const long long step,
+                                                                             const int par)
+{
+    __shared__ SplitLds<R, false> lds;
+    const int t = pass_tile(par);
+    const BatchJob J = jobs[job_of_tile(jobs, njobs, t)];
+    const int tile = t - J.tile_begin;
+    pass_split<MU, R, HIT1, DLT, false, false, BIG>((store_t<R> *)J.links, J.g, par, tile, sizeof(R) == 8 ? (R)J.q32 : (R)J.q32f,
+                                                    R(0), R(0), J.sweep0 + (uint64_t)(step - J.admit_step), J.seed,
+                                                    J.nhit, J.counters, tile % kCounterSlots, nullptr, lds);
+}
+// ---------------------------------------------------------------------------
+// launch
+// ---------------------------------------------------------------------------
+template <typename R> R q32_of(double beta) { return R(1.5) / R(beta); }
+
+template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG> void launch_one(const PassArgs &a)
+{
+    const unsigned grid = (unsigned)pass_blocks(a.g, kPassBlock);
+    const R q = TWOB ? R(1.5) : q32_of<R>(a.beta0), w0 = R(a.beta0), w1 = R(a.beta1);
+    k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG><<<grid, kSplitBlock, 0, a.stream>>>(
+        (store_t<R> *)a.links, a.g, a.par, q, w0, w1, a.sweep, a.seed, a.nhit, a.counters, a.meas);
+}
+
+template <int MU, typename R, bool MEAS, bool TWOB> void launch_mu(const PassArgs &a)
+{
+    // a lattice whose blocks reach 4 GiB: 64-bit offsets, in the variant that
+    // takes any hit count and any torus
+    if (a.big) return launch_one<MU, R, false, true, MEAS, TWOB, true>(a);
+    const bool hit1 = a.nhit == 1;
+    if constexpr (TWOB) {
+        if (hit1)
+            launch_one<MU, R, true, true, MEAS, TWOB, false>(a);
+        else
+            launch_one<MU, R, false, true, MEAS, TWOB, false>(a);
+    } else if (a.g.nlat == 2) {
+        if (hit1)
+            launch_one<MU, R, true, true, MEAS, TWOB, false>(a);
+        else
+            launch_one<MU, R, false, true, MEAS, TWOB, false>(a);
+    } else if (hit1) {
+        launch_one<MU, R, true, false, MEAS, TWOB, false>(a);
+    } else {
+        launch_one<MU, R, false, false, MEAS, TWOB, false>(a);
+    }
+}
+
+template <typename R, bool MEAS, bool TWOB> void launch_any(const PassArgs &a)
+{
+    switch (a.mu) {
+    case 0:
+        if constexpr (!MEAS) launch_mu<0, R, MEAS, TWOB>(a);
+        break;
+    case 1: launch_mu<1, R, MEAS, TWOB>(a); break;
+    case 2: launch_mu<2, R, MEAS, TWOB>(a); break;
+    default: launch_mu<3, R, MEAS, TWOB>(a); break;
+    }
+}
+
+template <typename R> hipError_t launch_pass_r(const PassArgs &a)
+{
+    if (a.twob)
+        launch_any<R, false, true>(a);
+    else if (a.meas)
+        launch_any<R, true, false>(a);
+    else
+        launch_any<R, false, false>(a);
+    return hipGetLastError();
+}
+
+template <int MU, typename R, bool HIT1, bool DLT, bool BIG> void launch_batch_one(const BatchArgs &b)
+{
+    k_batch_split<MU, R, HIT1, DLT, BIG><<<b.ntiles, kSplitBlock, 0, b.stream>>>(b.jobs, b.njobs, b.step, b.par);
+}
+
+template <int MU, typename R> void launch_batch_mu(const BatchArgs &b)
+{
+    if (b.big)
+        launch_batch_one<MU, R, false, true, true>(b);
+    else if (b.dlt && b.hit1)
+        launch_batch_one<MU, R, true, true, false>(b);
+    else if (b.dlt)
+        launch_batch_one<MU, R, false, true, false>(b);
+    else if (b.hit1)
+        launch_batch_one<MU, R, true, false, false>(b);
+    else
+        launch_batch_one<MU, R, false, false, false>(b);
+}
+
+template <typename R> hipError_t launch_batch_r(const BatchArgs &b)
+{
+    switch (b.mu) {
+    case 0: launch_batch_mu<0, R>(b); break;
+    case 1: launch_batch_mu<1, R>(b); break;
+    case 2: launch_batch_mu<2, R>(b); break;
+    default: launch_batch_mu<3, R>(b); break;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace su3hb

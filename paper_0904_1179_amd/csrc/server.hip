@@ -6,8 +6,7 @@
 // Every su3_server_step runs one sweep of every admitted job as 8 batched
 // launches (one per pass, all jobs of a precision in the same launch),
 // then retires the jobs that reached their sweep count: plaquette and
-// counters are copied back and their arena block is freed.  A small 1-hit
-// batch runs two lanes per link.  A job's links
+// counters are copied back and their arena block is freed.  A job's links
 // get exactly the per-link arithmetic of the single-lattice path and the
 // same keyed random numbers, so its result does not depend on what else runs.
 #include <hip/hip_runtime.h>
@@ -29,7 +28,6 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kGroups = 8;  // (precision 64/32) x (1-hit / general) x (single / double-layered torus)
-constexpr long long kBatchLanes2Max = 32768;
 
 size_t align_up(size_t a) { return (a + kAlign - 1) / kAlign * kAlign; }
 
@@ -49,6 +47,7 @@ struct Job {
 struct Group {
     BatchJob *d_table = nullptr;  // device copy
     int njobs = 0, ntiles = 0;
+    bool big = false;
 };
 
 }  // namespace
@@ -134,30 +133,25 @@ su3_status build_tables(su3_server *s)
         b.links = s->arena + j.off;
         b.counters = (unsigned long long *)(s->arena + j.off + j.link_bytes + kOffCounters);
         b.g = j.g;
-        b.beta = j.spec.beta;
+        b.q32 = 1.5 / j.spec.beta;
+        b.q32f = 1.5f / (float)j.spec.beta;
+        b.nhit = j.spec.params.nhit;
         b.seed = j.spec.params.seed;
         b.sweep0 = 0;
         b.admit_step = j.admit_step;
-        b.nhit = j.spec.params.nhit;
-        b.lanes = 1;
         b.tile_begin = 0;
         per[group_of(j.spec)].push_back(b);
     }
     for (int gi = 0; gi < kGroups; ++gi) {
         Group &G = s->groups[gi];
         BatchJob *h = s->h_table + (size_t)gi * s->max_active;
-        // a 1-hit batch of at most kBatchLanes2Max links per pass (fewer than
-        // one wave per SIMD) is bound by the latency of one update: two lanes
-        // per link shorten it (10^4 - 16^4 FP32: 12 % per sweep)
-        long long links = 0;
-        for (const BatchJob &b : per[gi]) links += (long long)b.g.nlat * b.g.Vh;
-        const int lanes = (gi & 2) == 0 && links <= kBatchLanes2Max ? 2 : 1;
         int tiles = 0;
+        G.big = false;
         for (size_t k = 0; k < per[gi].size(); ++k) {
             h[k] = per[gi][k];
-            h[k].lanes = lanes;
             h[k].tile_begin = tiles;
-            tiles += (int)(((long long)lanes * h[k].g.nlat * h[k].g.Vh + kPassBlock - 1) / kPassBlock);
+            tiles += pass_blocks(h[k].g, kPassBlock);
+            G.big = G.big || pass_big(h[k].g, gi < 4 ? 64 : 32);
         }
         G.d_table = (BatchJob *)s->arena + (size_t)gi * s->max_active;
         G.njobs = (int)per[gi].size();
@@ -281,8 +275,9 @@ su3_status run_sweeps(su3_server *s, int32_t max_sweeps, int32_t *n_active, int3
                     for (int gi = 0; gi < kGroups; ++gi) {
                         const Group &G = s->groups[gi];
                         if (!G.njobs) continue;
-                        e = launch_update_batch(gi < 4 ? 64 : 32, (gi & 2) == 0, (gi & 1) != 0, G.d_table, G.njobs,
-                                                G.ntiles, s->step, mu, par, s->stream);
+                        const BatchArgs b{G.d_table,     G.njobs,       G.ntiles, s->step, mu, par,
+                                          (gi & 2) == 0, (gi & 1) != 0, G.big,    s->stream};
+                        e = launch_batch(gi < 4 ? 64 : 32, b);
                         if (e != hipSuccess) return hip_fail(e, "batched pass");
                     }
             s->step += 1;
