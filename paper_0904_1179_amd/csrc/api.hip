@@ -4,7 +4,7 @@
 // point validates its arguments before touching HIP, enqueues work on the
 // context's stream and reports failures as su3_status plus a thread-local
 // message.  A sweep is the 8-pass schedule mu = 0..3 x parity (even, odd),
-// each pass one k_update launch; the sweep index keys the random numbers.
+// each pass one launch; the sweep index keys the random numbers.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -168,6 +168,7 @@ su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nul
     a.beta1 = betas ? betas[1] : beta;
     a.twob = betas != nullptr;
     a.big = pass_big(c->g, c->p.precision);
+    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, pass_blocks(c->g, kPassBlock));
     a.seed = c->p.seed;
     a.nhit = c->p.nhit;
     a.counters = counters_of(c);

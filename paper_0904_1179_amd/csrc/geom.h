@@ -70,6 +70,7 @@ struct Geom {
     int nlat;
     unsigned flip;      // layer-switch mask, 0 on a single torus
     long long stride;   // links per (direction, parity) block (>= nlat * Vh, multiple of 64)
+    int hs[4], wrap[4]; // half-index steps along each direction and (L - 1) times them (hs[0] = 1, wrap[0] = L0/2 - 1)
     int w1, w2;         // domain widths of the pass order (divide L1, L2)
     int nd1;            // L1 / w1
     FastDiv dl0h, dl1, dl2, dl3, dw1, dw2, dnd1;  // division by L0/2, L1, L2, L3, w1, w2, nd1

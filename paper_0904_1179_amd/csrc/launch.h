@@ -31,6 +31,7 @@ struct PassArgs {
     double beta0, beta1;           // the coupling, or one per layer (twob)
     bool twob;                     // double-layered torus: a plaquette takes its base site's layer coupling
     bool big;                      // 64-bit link offsets (pass_big)
+    bool six_waves;                // six waves per 64 links instead of three (pass_six_waves)
     uint64_t sweep, seed;
     int nhit;
     unsigned long long *counters;
@@ -61,7 +62,7 @@ struct BatchArgs {
     int njobs, ntiles;
     long long step;
     int mu, par;
-    bool hit1, dlt, big;
+    bool hit1, dlt, big, six_waves;
     hipStream_t stream;
 };
 hipError_t launch_batch_f64(const BatchArgs &b);

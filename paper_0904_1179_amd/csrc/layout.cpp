@@ -95,6 +95,14 @@ Geom make_geom(const su3_params *p)
     // power-of-two spacing, so equal positions in different blocks do not all
     // fall in the same L2 channel and set
     g.stride = round_up((long long)p->nlat * (V / 2), 64) + 64;
+    // a step along direction 0 moves the half-index by 0 or 1; the others by
+    // half the lexicographic stride, which is even
+    g.hs[0] = 1;
+    g.wrap[0] = p->L[0] / 2 - 1;
+    for (int mu = 1, h = p->L[0] / 2; mu < 4; h *= p->L[mu], ++mu) {
+        g.hs[mu] = h;
+        g.wrap[mu] = (p->L[mu] - 1) * h;
+    }
     pick_domains(p->L, p->nlat, g.w1, g.w2);
     g.nd1 = p->L[1] / g.w1;
     g.dl0h = make_fastdiv((uint32_t)(p->L[0] / 2));
@@ -128,6 +136,21 @@ int lanes_per_link(const Geom &g, int nhit, int requested)
 bool pass_big(const Geom &g, int precision)
 {
     return (unsigned long long)g.stride * kEntries * (precision == 64 ? 16u : 8u) >= (1ull << 32);
+}
+
+// Six waves per tile instead of three take the draws out of the chain that a
+// pass with few tiles waits for; with more tiles than run at once only the
+// number of instructions and the waves per SIMD count, and six waves hold
+// their registers until the slowest ends.  us per pass, six against three waves:
+//   FP64          256 tiles 6.5 / 7.2, 512 8.5 / 9.2, 576 11.4 / 10.9 (two
+//                 workgroups of 128 registers per CU fill 256 CUs at 512);
+//   FP64, 3 hits  256 tiles 10.0 / 11.2, 384 13.7 / 13.1 (six waves make every
+//                 second draw, three only the likely ones);
+//   FP32          768 tiles 8.3 / 8.6, 1024 9.6 / 9.5;
+//   FP32, 3 hits  512 tiles 9.8 / 11.0, 576 11.6 / 11.4.
+bool pass_six_waves(int precision, bool hit1, long long tiles)
+{
+    return tiles <= (precision == 64 ? (hit1 ? 512 : 256) : (hit1 ? 768 : 512));
 }
 
 int pass_links_per_block(const Geom &, int) { return kPassBlock; }

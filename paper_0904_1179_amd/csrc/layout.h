@@ -33,6 +33,9 @@ int lanes_per_link(const Geom &g, int nhit, int requested);
 // Whether a (direction, parity) block reaches 4 GiB, so that link offsets need
 // 64 bits.
 bool pass_big(const Geom &g, int precision);
+// Whether a pass of that many tiles of 64 links gives the random draws to three
+// waves of their own.
+bool pass_six_waves(int precision, bool hit1, long long tiles);
 // Links per workgroup of a pass (64, whatever the lanes).
 int pass_links_per_block(const Geom &g, int lanes);
 // workgroups covering the nlat * Vh links of one pass, nb links each

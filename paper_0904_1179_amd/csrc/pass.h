@@ -42,9 +42,13 @@ template <typename R, bool BIG> __device__ __forceinline__ offset_t<BIG> link_of
 template <typename R> struct Block {
     const char *base;
 };
-template <typename R> __device__ __forceinline__ Block<R> block_of(const store_t<R> *links, const Geom &g, int dir, int par)
+template <typename R, bool BIG = true>
+__device__ __forceinline__ Block<R> block_of(const store_t<R> *links, const Geom &g, int dir, int par)
 {
-    return Block<R>{(const char *)(links + (size_t)(dir * 2 + par) * (size_t)g.stride * kEntries)};
+    constexpr uint32_t kLink = kEntries * sizeof(store_t<R>);
+    if constexpr (BIG) return Block<R>{(const char *)links + (size_t)(dir * 2 + par) * (size_t)g.stride * kLink};
+    // a block has less than 4 GiB
+    return Block<R>{(const char *)links + (uint64_t)(uint32_t)(dir * 2 + par) * ((uint32_t)g.stride * kLink)};
 }
 
 // Rows 0 and 1 of the link at offset o (row 2 is left undefined).
@@ -131,29 +135,11 @@ struct Step {
 };
 template <int D, int S> __device__ __forceinline__ Step step_of(const Geom &g, const Site &s)
 {
-    const int h = g.L[0] >> 1;
+    const bool edge = S > 0 ? s.x[D] == g.L[D] - 1 : s.x[D] == 0;
+    const int odd = s.x[0] & 1;
+    const int by = D != 0 ? g.hs[D] : S > 0 ? odd : 1 - odd;
     Step r;
-    bool edge;
-    if constexpr (D == 0) {
-        const bool odd = s.x[0] & 1;
-        if constexpr (S > 0) {
-            edge = s.x[0] == g.L[0] - 1;
-            r.di = edge ? 1 - h : (odd ? 1 : 0);
-        } else {
-            edge = s.x[0] == 0;
-            r.di = edge ? h - 1 : (odd ? 0 : -1);
-        }
-    } else {
-        const int hs = D == 1 ? h : D == 2 ? h * g.L[1] : h * g.L[1] * g.L[2];
-        const int wrap = (g.L[D] - 1) * hs;
-        if constexpr (S > 0) {
-            edge = s.x[D] == g.L[D] - 1;
-            r.di = edge ? -wrap : hs;
-        } else {
-            edge = s.x[D] == 0;
-            r.di = edge ? wrap : -hs;
-        }
-    }
+    r.di = S > 0 ? (edge ? -g.wrap[D] : by) : (edge ? g.wrap[D] : -by);
     r.flip = edge ? (int)((g.flip >> D) & 1u) : 0;
     return r;
 }
@@ -170,22 +156,29 @@ template <bool DLT> __device__ __forceinline__ int elem(const Geom &g, const Sit
     return DLT ? i + ((s.layer ^ a.flip ^ b.flip) ? g.Vh : 0) : i;
 }
 
-// The two steps along a direction known at run time (uniform over the wave).
-template <int MU> __device__ __forceinline__ void steps_of(const Geom &g, const Site &s, int nu, Step &up, Step &dn)
+// The staple directions nu != MU in increasing order.
+template <int MU> constexpr int kNu0 = MU == 0 ? 1 : 0;
+template <int MU> constexpr int kNu1 = MU <= 1 ? 2 : 1;
+template <int MU> constexpr int kNu2 = MU <= 2 ? 3 : 2;
+
+// The two steps along the direction of wave w (2, 0, 1 of the staple
+// directions for w = 0, 1, 2): step_of with the direction chosen by selects
+// that are uniform over the wave, without branches.
+template <int MU, bool DLT>
+__device__ __forceinline__ void steps_of(const Geom &g, const Site &s, int w, Step &up, Step &dn)
 {
-    if (MU != 0 && nu == 0) {
-        up = step_of<0, +1>(g, s);
-        dn = step_of<0, -1>(g, s);
-    } else if (MU != 1 && nu == 1) {
-        up = step_of<1, +1>(g, s);
-        dn = step_of<1, -1>(g, s);
-    } else if (MU != 2 && nu == 2) {
-        up = step_of<2, +1>(g, s);
-        dn = step_of<2, -1>(g, s);
-    } else {
-        up = step_of<3, +1>(g, s);
-        dn = step_of<3, -1>(g, s);
-    }
+    constexpr int A = kNu2<MU>, B = kNu0<MU>, C = kNu1<MU>;
+    const auto pick = [w](int a, int b, int c) { return w == 0 ? a : w == 1 ? b : c; };
+    const int x = pick(s.x[A], s.x[B], s.x[C]), L = pick(g.L[A], g.L[B], g.L[C]);
+    const int hs = pick(g.hs[A], g.hs[B], g.hs[C]), wrap = pick(g.wrap[A], g.wrap[B], g.wrap[C]);
+    const int odd = s.x[0] & 1;
+    const bool along0 = B == 0 && w == 1;
+    const bool top = x == L - 1, bottom = x == 0;
+    up.di = top ? -wrap : along0 ? odd : hs;
+    dn.di = bottom ? wrap : along0 ? odd - 1 : -hs;
+    const int bit = DLT ? (int)((g.flip >> pick(A, B, C)) & 1u) : 0;
+    up.flip = DLT && top ? bit : 0;
+    dn.flip = DLT && bottom ? bit : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -265,23 +258,39 @@ __device__ __forceinline__ StapleAt<BIG> staple_at(const Geom &g, const Site &s,
     return a;
 }
 
+// How many of the six links of a direction are requested before the random
+// draw.  More cost registers, and so waves that share a SIMD: FP64 four (152
+// registers, three waves; with two 8^4 takes 460 instead of 420 us per 8
+// sweeps, 16^4 708 instead of 676 us), FP32 two (six waves; with four 16^4
+// takes 525 instead of 508 us, a batch of jobs 22.4 instead of 22.1 ms).
+template <typename R> constexpr int kEarlyLinks = sizeof(R) == 8 ? 4 : 2;
+
 // The two staples of direction nu.  TWOB: FP64 D = w[layer] up + w[base layer
 // of the lower plaquette] dn; FP32 D = up and cross = dn, to be weighted where
-// they are added.
-template <int MU, typename R, bool CROSS, bool TWOB, bool BIG>
+// they are added.  between(): work that needs none of the links, done while
+// the first kEarlyLinks are on their way (the compiler would sink the loads or
+// hoist the products, hence the barriers).
+template <int MU, typename R, bool CROSS, bool TWOB, bool BIG, typename Between>
 __device__ __forceinline__ void staple_nu(M3<R> &D, M3<R> &cross, const store_t<R> *links, const Geom &g, int par, int nu,
-                                          const StapleAt<BIG> &at, int layer, R w0, R w1)
+                                          const StapleAt<BIG> &at, int layer, R w0, R w1, Between between)
 {
     const int opp = par ^ 1;
-    const Block<R> umu = block_of<R>(links, g, MU, opp), unu_par = block_of<R>(links, g, nu, par),
-                   unu_opp = block_of<R>(links, g, nu, opp);
+    const Block<R> umu = block_of<R, BIG>(links, g, MU, opp), unu_par = block_of<R, BIG>(links, g, nu, par),
+                   unu_opp = block_of<R, BIG>(links, g, nu, opp);
     M3<R> b, e, c, d, a, f;
     load_rows_pair(b, umu, at.up, e, umu, at.dn);
-    load_rows_pair(c, unu_par, at.here, d, unu_par, at.mu_dn);
-    load_rows_pair(a, unu_opp, at.mu, f, unu_opp, at.dn);
+    if constexpr (kEarlyLinks<R> == 4) load_rows_pair(c, unu_par, at.here, d, unu_par, at.mu_dn);
+    __builtin_amdgcn_sched_barrier(0);
+    between();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kEarlyLinks<R> == 2) {
+        load_rows_pair(c, unu_par, at.here, d, unu_par, at.mu_dn);
+        load_rows_pair(a, unu_opp, at.mu, f, unu_opp, at.dn);
+    }
     rebuild_row2(b);
     rebuild_row2(d);
     const M3<R> cb = mul_nn_su3(c, b);
+    if constexpr (kEarlyLinks<R> == 4) load_rows_pair(a, unu_opp, at.mu, f, unu_opp, at.dn);
     const M3<R> ed = mul_nn_su3(e, d);
     D = mul_nd_su3(a, cb);
     rebuild_row2(f);
@@ -353,7 +362,29 @@ template <typename R> __device__ __forceinline__ KPDraw<R> kp_draw(uint32_t lid,
     return d;
 }
 
-// A draw of attempt 0 in LDS, slot-major over the 64 lanes.
+// A matrix in LDS, entry-major over the 64 lanes.
+template <typename R, int N> __device__ __forceinline__ void lds_put(store_t<R> (*buf)[64], int lane, const M3<R> &m)
+{
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        store_t<R> v;
+        v.x = m.e[e / 3][e % 3].re;
+        v.y = m.e[e / 3][e % 3].im;
+        buf[e][lane] = v;
+    }
+}
+template <typename R, int N> __device__ __forceinline__ M3<R> lds_get(const store_t<R> (*buf)[64], int lane)
+{
+    M3<R> m;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const store_t<R> v = buf[e][lane];
+        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
+    }
+    return m;
+}
+
+// A draw in LDS, slot-major over the 64 lanes.
 template <typename R> __device__ __forceinline__ void draw_put(store_t<R> (*buf)[64], int lane, const KPDraw<R> &d)
 {
     store_t<R> a, b, c;
@@ -379,15 +410,35 @@ struct Counts {
 };
 __device__ __forceinline__ uint32_t lanes_of(bool p) { return (uint32_t)__popcll(__ballot(p)); }
 
-// The heat bath proper.  first(sub): the draw of attempt 0.  q32 = 3/(2 beta).
+// Second attempts made ahead by three waves.  An attempt misses where u4^2 >
+// 1 - lambda^2; lambda^2 is a few per cent at the usual couplings, so all but
+// some misses in a thousand have u4^2 above kMayMiss: 22.5 % of the lanes, 14 of 64, of
+// which two do miss.  The second draws of the first kPoolSlots of these lanes, for all
+// three subgroups, are made together by one wave: a third of the work of
+// drawing for every lane.  A lane that misses without one draws when it does.
+constexpr int kPoolSlots = 21;
+constexpr double kMayMiss = 0.6;
+template <typename R> __device__ __forceinline__ int pool_slot(R u4sq, int sub, int lane)
+{
+    const bool may = u4sq > R(kMayMiss);
+    const uint64_t m = __ballot(may);
+    const int rank = __popcll(m & ((1ull << lane) - 1));
+    return may && rank < kPoolSlots ? sub * kPoolSlots + rank : -1;
+}
+
+// The heat bath proper.  first(sub): the draw of attempt 0, made ahead;
+// second(sub, u4sq, made): that of attempt 1 where made is set (several
+// attempts; u4sq: the first draw's).  q32 = 3/(2 beta).  park: 18 entries per
+// lane of LDS (several attempts).
 // All 64 lanes take part; only the `active` ones count.  There is no branch
 // per lane: a rejected attempt (3 % of them, so nearly every wave has one)
 // rotates by the identity, which leaves finite rows as they are.  Returns
 // Re Tr W after the last subgroup, i.e. Re Tr(U_new A) before the final
 // reunitarisation.  Projections are of 2 v; the factor is exact and cancels.
-template <typename R, bool HIT1, typename First>
+template <typename R, bool HIT1, typename First, typename Second>
 __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint32_t lid, uint64_t sweep, uint64_t seed,
-                                           int nhit, bool active, Counts &n, First first)
+                                           int nhit, bool active, Counts &n, store_t<R> (*park)[64], int lane,
+                                           First first, Second second)
 {
     M3<R> W = mul_nn(U, A);
 #pragma unroll
@@ -400,29 +451,49 @@ __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint
         const R v3 = W.e[j][j].im - W.e[i][i].im;
         const R k2 = v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
         // a staple projection that vanishes exactly: nothing to sample, no attempt
-        bool todo = k2 != R(0);
+        const bool sample = k2 != R(0);
         const R rk = rsqrt_r(k2);
         const R inv2alpha = q32 * rk;
-        bool ok = false;
-        R a0 = R(1), a1 = R(0), a2 = R(0), a3 = R(0);
-        auto attempt = [&](const KPDraw<R> &d) {
-            const R lam2 = -d.q * inv2alpha;
-            const bool hit = todo && d.u4sq <= R(1) - lam2;
-            n.att += lanes_of(todo && active);
-            n.acc += lanes_of(hit && active);
-            const R b0 = R(1) - R(2) * lam2;
-            const R rho2 = R(1) - b0 * b0;
-            const R rho = rho2 > R(0) ? sqrt_pos_r(rho2) : R(0);
-            a0 = hit ? b0 : a0;
-            a1 = hit ? rho * d.sc : a1;
-            a2 = hit ? rho * d.ss : a2;
-            a3 = hit ? rho * d.cth : a3;
-            ok = ok || hit;
-            todo = todo && !hit;
-        };
-        attempt(first(sub));
-        if constexpr (!HIT1)
-            for (int t = 1; t < nhit && __ballot(todo) != 0; ++t) attempt(kp_draw<R>(lid, sweep, seed, sub, t));
+        KPDraw<R> d = first(sub);
+        R lam2 = -d.q * inv2alpha;
+        bool ok = sample && d.u4sq <= R(1) - lam2;
+        n.att += lanes_of(sample && active);
+        n.acc += lanes_of(ok && active);
+        if constexpr (!HIT1) {
+            // a lane that has missed takes the next draw's values if that one hits
+            auto again = [&](const KPDraw<R> &e, bool turn) {
+                const R l = -e.q * inv2alpha;
+                const bool hit = turn && e.u4sq <= R(1) - l;
+                n.att += lanes_of(turn && active);
+                n.acc += lanes_of(hit && active);
+                lam2 = hit ? l : lam2;
+                d.cth = hit ? e.cth : d.cth;
+                d.sc = hit ? e.sc : d.sc;
+                d.ss = hit ? e.ss : d.ss;
+                ok = ok || hit;
+            };
+            bool made = false;
+            if (nhit > 1) {
+                const KPDraw<R> e = second(sub, d.u4sq, made);
+                again(e, sample && !ok && made);
+            }
+            // rare: U and W wait in LDS, so that the draw has the registers
+            for (int t = __ballot(sample && !ok && !made) != 0 ? 1 : 2; t < nhit && __ballot(sample && !ok) != 0; ++t) {
+                const bool turn = sample && !ok && (t > 1 || !made);
+                lds_put<R, 9>(park, lane, U);
+                lds_put<R, 9>(park + 9, lane, W);
+                __asm__ __volatile__("" ::: "memory");
+                const KPDraw<R> e = kp_draw<R>(lid, sweep, seed, sub, t);
+                __asm__ __volatile__("" ::: "memory");
+                U = lds_get<R, 9>(park, lane);
+                W = lds_get<R, 9>(park + 9, lane);
+                again(e, turn);
+            }
+        }
+        const R a0 = R(1) - R(2) * lam2;
+        const R rho2 = R(1) - a0 * a0;
+        const R rho = rho2 > R(0) ? sqrt_pos_r(rho2) : R(0);
+        const R a1 = rho * d.sc, a2 = rho * d.ss, a3 = rho * d.cth;
         const R b0 = v0 * rk, b1 = v1 * rk, b2 = v2 * rk, b3 = v3 * rk;
         // quaternion product c = a * b  <=>  P(c) = P(a) P(b)
         const R p0 = a0 * b0 - a1 * b1 - a2 * b2 - a3 * b3;
@@ -487,33 +558,6 @@ __device__ __forceinline__ int pass_tile(int par)
 {
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     return par ? (int)gridDim.x - 1 - t : t;
-}
-
-// The staple directions nu != MU in increasing order.
-template <int MU> constexpr int kNu0 = MU == 0 ? 1 : 0;
-template <int MU> constexpr int kNu1 = MU <= 1 ? 2 : 1;
-template <int MU> constexpr int kNu2 = MU <= 2 ? 3 : 2;
-
-// A matrix in LDS, entry-major over the 64 lanes.
-template <typename R, int N> __device__ __forceinline__ void lds_put(store_t<R> (*buf)[64], int lane, const M3<R> &m)
-{
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-        store_t<R> v;
-        v.x = m.e[e / 3][e % 3].re;
-        v.y = m.e[e / 3][e % 3].im;
-        buf[e][lane] = v;
-    }
-}
-template <typename R, int N> __device__ __forceinline__ M3<R> lds_get(const store_t<R> (*buf)[64], int lane)
-{
-    M3<R> m;
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-        const store_t<R> v = buf[e][lane];
-        m.e[e / 3][e % 3] = Cx<R>{v.x, v.y};
-    }
-    return m;
 }
 
 }  // namespace

@@ -3,53 +3,103 @@
 // (pass_f64.hip, pass_f32.hip).
 #pragma once
 
+#include <type_traits>
+
 #include "pass.h"
 
 namespace su3hb {
 namespace {
 
-constexpr int kSplitBlock = 192;  // threads per workgroup of the split pass: three waves for 64 links
-
-// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed
-// and 128 taken by the unmeasured passes, so four waves share a SIMD.  Asked
-// for four, the compiler schedules for registers and the pass is 10 % slower;
-// held to exactly three waves it is 3 % slower.
+// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed;
+// three waves per tile take 152, six 128, so that four waves share a SIMD.
+// Asked for four, the compiler schedules for registers and the pass is 10 %
+// slower; held to exactly three waves it is 3 % slower.
 template <typename R> constexpr int kSplitWaves = sizeof(R) == 8 ? 3 : 5;
 
 // FP32 with per-layer couplings keeps the six staple terms apart (D: the two
 // of a direction one after the other).
 template <typename R, bool TWOB> constexpr bool kTermsApart = TWOB && sizeof(R) == 4;
 
-template <typename R, bool TWOB> struct SplitLds {
-    store_t<R> D[2][kTermsApart<R, TWOB> ? 18 : 9][64];  // D of the first two directions
-    store_t<R> draw[2][3][64];                           // draws of subgroups 0 and 1
+// Several attempts: the second draws.  Six waves make them for every link and
+// subgroup; three for the lanes that pool_slot picks, whose links are listed.
+template <typename R, bool HIT1, bool SIX> struct SecondDraws {};
+template <typename R> struct SecondDraws<R, false, true> {
+    store_t<R> second[3][3][64];
 };
+template <typename R> struct SecondDraws<R, false, false> {
+    store_t<R> pool[3][64];
+    uint32_t list[64];
+};
+
+template <typename R, bool HIT1, bool TWOB, bool KEEP, bool SIX> struct SplitLds : SecondDraws<R, HIT1, SIX> {
+    store_t<R> D[2][kTermsApart<R, TWOB> ? 18 : 9][64];  // D of the first two directions
+    store_t<R> draw[SIX ? 3 : 2][3][64];
+    // where U and W wait for a further attempt: over D, unless a measurement reads it later
+    __device__ store_t<R> (*parking())[64] { return D[0]; }
+};
+template <typename R, bool TWOB, bool SIX> struct SplitLds<R, false, TWOB, true, SIX> : SecondDraws<R, false, SIX> {
+    store_t<R> D[2][9][64];
+    store_t<R> draw[SIX ? 3 : 2][3][64];
+    store_t<R> park[18][64];
+    __device__ store_t<R> (*parking())[64] { return park; }
+};
+// A measured pass of a double-layered torus.
+template <typename R, bool HIT1, int MU, bool SIX> struct CrossLds : SplitLds<R, HIT1, false, true, SIX> {
+    store_t<R> U[9][64];                // the new link
+    store_t<R> X[MU == 3 ? 9 : 1][64];  // wave 0's cross-layer part
+    double part[3][2];
+};
+template <typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, int MU, bool SIX>
+using PassLds = std::conditional_t<MEAS && DLT, CrossLds<R, HIT1, MU, SIX>, SplitLds<R, HIT1, TWOB, MEAS, SIX>>;
+
+// A wave's share of a measured tile per layer: tr is filed under the link's
+// layer but for its part trx, which belongs to the other one.
+template <typename Lds>
+__device__ __forceinline__ void cross_share(Lds &lds, bool active, bool l1, double tr, double trx, int w, int lane)
+{
+    const double s0 = wave_sum(active ? (l1 ? trx : tr - trx) : 0.0);
+    const double s1 = wave_sum(active ? (l1 ? tr - trx : trx) : 0.0);
+    if (lane == 0) {
+        lds.part[w][0] = s0;
+        lds.part[w][1] = s1;
+    }
+}
 
 // One tile of 64 links with three waves: wave w forms the two staples of one
 // direction and the random draw of one subgroup for all 64 links, and wave 0
-// then adds the three and runs the heat bath.
+// then adds the three and runs the heat bath.  SIX: three more waves make the
+// draws (pass_six_waves says when).
 //
 // One lane per link, all in one thread, takes 3900 instructions (FP64) and 220
 // registers: two waves per SIMD, each of which spends a third of its time on
 // memory while the other alone issues at half rate.  Here no wave has more
-// than one direction in registers (128 in FP64, 75 in FP32), the six loads of
-// U_mu(x +- nu) that all directions share are in flight together, the chain
-// from the first load to the store is 1560 instructions instead of 3900, and
-// nothing is computed twice but the addresses: 3340 instructions per 64 links
-// in all.  Time per pass, one lane per link (up to 8192 links four, up to
-// 32768 two) -> three waves:
-//   FP64  8^4 9.5 -> 6.7, 16^4 13.1 -> 10.1, 2 x 16^4 18.2 -> 16.2, 24^4 35.4 ->
-//         31.2, 32^4 96.6 -> 88.5, 64^4 1604 -> 1563 us;
-//   FP32  16^4 10.9 -> 8.8, 2 x 16^4 14.0 -> 12.1, 24^4 22.0 -> 19.9, 32^4 50.2 ->
-//         48.7 us, 64^4 865 us either way.
+// than one direction in registers (152 in FP64, 128 without the draws, 77 in
+// FP32), the loads of four links (FP32: two) are in flight while the draw is
+// made, the chain from the first load to the store is 1525 instructions
+// instead of 3900 (1100 with six waves), and nothing is computed twice but the
+// addresses.  us per pass, one lane per link (up to 8192 links four, up to
+// 32768 two) -> this:
+//   FP64          8^4 9.6 -> 5.9, 16^4 12.9 -> 8.6, 2 x 16^4 18.1 -> 15.2, 24^4 35.4
+//                 -> 29.7, 32^4 96 -> 88, 64^4 1605 -> 1553;
+//   FP64, 3 hits  8^4 16.2 -> 8.8, 16^4 18.4 -> 13.6, 32^4 106 -> 101, 64^4 1740 -> 1720;
+//   FP32          8^4 9.1 -> 5.8, 16^4 10.7 -> 7.3, 2 x 16^4 14.0 -> 10.3, 24^4 22.2 ->
+//                 19.3, 32^4 49.9 -> 46.7, 64^4 854 -> 837;
+//   FP32, 3 hits  16^4 19.2 -> 9.8, 32^4 65 -> 56, 64^4 1030 -> 955;
+//   measured, two layers, 2 x 16^4: FP64 19.3 -> 17.3, FP32 15.4 -> 11.6.
 // What bounds it now: 32^4 FP64 moves 500 MB past L2 at 5.7 TB/s with the
-// vector unit 54 % busy; FP32 keeps it 86 % busy; 8^4 has an eighth of a wave
+// vector unit 57 % busy (its loads and stores alone take 76 us, its arithmetic
+// alone 64); FP32 keeps the vector unit 86 % busy; 8^4 has a quarter of a wave
 // per SIMD and takes the chain's latency.
-template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG>
+//
+// Several attempts: three waves make the first draws while the links arrive,
+// wave 1 then the pool's second ones while wave 0 multiplies U by the staple.
+// Second draws for every link instead: 32^4 FP64 111, FP32 59 us.
+template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG, bool SIX>
 __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const Geom &g, int par, int tile, R q32, R w0,
                                            R w1, uint64_t sweep, uint64_t seed, int nhit,
                                            unsigned long long *__restrict__ counters, int slot,
-                                           double *__restrict__ meas, SplitLds<R, TWOB> &lds)
+                                           double *__restrict__ meas,
+                                           PassLds<R, HIT1, DLT, MEAS, TWOB, MU, SIX> &lds)
 {
     static_assert(!MEAS || (MU > 0 && !TWOB), "measured passes: MU = 1, 2, 3 with one coupling");
     constexpr bool CROSS = MEAS && DLT;
@@ -60,96 +110,139 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
     const bool active = v < nlinks;
     v = active ? v : nlinks - 1;  // a lane past the end works on the last link and stores nothing
     const Site s = site_of<DLT>(g, par, v);
-    const int nu = w == 0 ? kNu2<MU> : w == 1 ? kNu0<MU> : kNu1<MU>;
-    const int sub = w == 0 ? 2 : w - 1;
-    Step up, dn;
-    steps_of<MU>(g, s, nu, up, dn);
-    const StapleAt<BIG> at = staple_at<MU, R, DLT, BIG>(g, s, step_of<MU, +1>(g, s), up, dn);
     const uint32_t lid = 4u * (uint32_t)(s.layer * 2 * g.Vh + 2 * s.i + (s.x[0] & 1)) + MU;
+    if constexpr (SIX)
+        if (w >= 3) {
+            draw_put<R>(lds.draw[w - 3], lane, kp_draw<R>(lid, sweep, seed, w - 3, 0));
+            if constexpr (!HIT1)
+                if (nhit > 1) draw_put<R>(lds.second[w - 3], lane, kp_draw<R>(lid, sweep, seed, w - 3, 1));
+            __syncthreads();
+            if constexpr (CROSS) {
+                __syncthreads();
+                __syncthreads();
+            }
+            return;
+        }
+    const int nu = w == 0 ? kNu2<MU> : w == 1 ? kNu0<MU> : kNu1<MU>;
+    Step up, dn;
+    steps_of<MU, DLT>(g, s, w, up, dn);
+    const StapleAt<BIG> at = staple_at<MU, R, DLT, BIG>(g, s, step_of<MU, +1>(g, s), up, dn);
     // D: the direction's sum; X: its part whose base lies in the other layer
     // (CROSS), or the lower term (kTermsApart; D is then the upper one)
     M3<R> D, X;
-    staple_nu<MU, R, CROSS, TWOB, BIG>(D, X, links, g, par, nu, at, s.layer, w0, w1);
-    const KPDraw<R> mine = kp_draw<R>(lid, sweep, seed, sub, 0);
+    KPDraw<R> mine;  // three waves: the draw of subgroup w - 1, or 2 for wave 0, which keeps it
+    staple_nu<MU, R, CROSS, TWOB, BIG>(D, X, links, g, par, nu, at, s.layer, w0, w1, [&] {
+        if constexpr (!SIX) {
+            const int sub = w == 0 ? 2 : w - 1;
+            mine = kp_draw<R>(lid, sweep, seed, sub, 0);
+            if constexpr (!HIT1) {
+                const int slot = pool_slot(mine.u4sq, sub, lane);
+                if (slot >= 0) lds.list[slot] = lid;
+            }
+        }
+    });
     if (w != 0) {
         lds_put<R, 9>(lds.D[w - 1], lane, D);
         if constexpr (kTermsApart<R, TWOB>) lds_put<R, 9>(lds.D[w - 1] + 9, lane, X);
-        draw_put<R>(lds.draw[w - 1], lane, mine);
+        if constexpr (!SIX) draw_put<R>(lds.draw[w - 1], lane, mine);
+        __syncthreads();
+        if constexpr (!SIX && !HIT1)
+            if (nhit > 1) {
+                if (w == 1) {
+                    // slots past a subgroup's candidates hold no link: their draws are not read
+                    const int sub = lane < kPoolSlots ? 0 : lane < 2 * kPoolSlots ? 1 : 2;
+                    draw_put<R>(lds.pool, lane, kp_draw<R>(lds.list[lane], sweep, seed, sub, 1));
+                }
+                __syncthreads();
+            }
+        if constexpr (CROSS) {
+            __syncthreads();
+            double trx = 0.0;
+            if (nu < MU) trx = retr_mul(lds_get<R, 9>(lds.U, lane), X);
+            cross_share(lds, active, s.layer != 0, 0.0, trx, w, lane);
+            __syncthreads();
+        }
+        return;
     }
-    const Block<R> own = block_of<R>(links, g, MU, par);
+    const Block<R> own = block_of<R, BIG>(links, g, MU, par);
     M3<R> U;
-    if (w == 0) load_own(U, own, at.here);
+    load_own(U, own, at.here);
+    if constexpr (CROSS && MU == 3) lds_put<R, 9>(lds.X, lane, X);
     __syncthreads();
-    double tr = 0.0, trx = 0.0;
-    if (w == 0) {
-        M3<R> A;
-        if constexpr (kTermsApart<R, TWOB>) {
-            // each term weighted and added in turn
-            const R wu = s.layer ? w1 : w0;
-            auto lower = [&](Step d) { return (s.layer ^ d.flip) ? w1 : w0; };
-            set_zero(A);
-            scale_acc(A, lds_get<R, 9>(lds.D[0], lane), wu);
-            scale_acc(A, lds_get<R, 9>(lds.D[0] + 9, lane), lower(step_of<kNu0<MU>, -1>(g, s)));
-            scale_acc(A, lds_get<R, 9>(lds.D[1], lane), wu);
-            scale_acc(A, lds_get<R, 9>(lds.D[1] + 9, lane), lower(step_of<kNu1<MU>, -1>(g, s)));
-            scale_acc(A, D, wu);
-            scale_acc(A, X, lower(dn));
-        } else {
-            A = lds_get<R, 9>(lds.D[0], lane);
-            add_to(A, lds_get<R, 9>(lds.D[1], lane));
-            add_to(A, D);
-        }
-        rebuild_row2(U);
-        Counts n{0, 0};
-        tr = heatbath<R, HIT1>(U, A, q32, lid, sweep, seed, nhit, active, n,
-                               [&](int k) { return k < 2 ? draw_get<R>(lds.draw[k], lane) : mine; });
-        if (active) store_own(own, at.here, U);
-        add_counts(n, counters, slot, lane);
-        if constexpr (MEAS) {
-            // S = sum of D_nu over nu < MU
-            if constexpr (MU == 1) tr = retr_mul(U, lds_get<R, 9>(lds.D[0], lane));
-            if constexpr (MU == 2) {
-                M3<R> S = lds_get<R, 9>(lds.D[0], lane);
-                add_to(S, lds_get<R, 9>(lds.D[1], lane));
-                tr = retr_mul(U, S);
-            }
-            if constexpr (!CROSS) {
-                tr = wave_sum(active ? tr : 0.0);
-                if (lane == 0) meas[0] = tr;
-            }
-        }
+    M3<R> A;
+    if constexpr (kTermsApart<R, TWOB>) {
+        // each term weighted and added in turn
+        const R wu = s.layer ? w1 : w0;
+        auto lower = [&](Step d) { return (s.layer ^ d.flip) ? w1 : w0; };
+        set_zero(A);
+        scale_acc(A, lds_get<R, 9>(lds.D[0], lane), wu);
+        scale_acc(A, lds_get<R, 9>(lds.D[0] + 9, lane), lower(step_of<kNu0<MU>, -1>(g, s)));
+        scale_acc(A, lds_get<R, 9>(lds.D[1], lane), wu);
+        scale_acc(A, lds_get<R, 9>(lds.D[1] + 9, lane), lower(step_of<kNu1<MU>, -1>(g, s)));
+        scale_acc(A, D, wu);
+        scale_acc(A, X, lower(dn));
+    } else {
+        A = lds_get<R, 9>(lds.D[0], lane);
+        add_to(A, lds_get<R, 9>(lds.D[1], lane));
+        add_to(A, D);
     }
-    if constexpr (CROSS) {
-        // the lower terms whose base lies in the other layer: each wave sums
-        // its own direction's share Re Tr(U_new X)
-        __shared__ double part[3][2];
-        __syncthreads();  // wave 0 has read D
-        if (w == 0) lds_put<R, 9>(lds.D[0], lane, U);
-        __syncthreads();
-        if (nu < MU) trx = retr_mul(lds_get<R, 9>(lds.D[0], lane), X);
-        const bool l1 = s.layer != 0;
-        const double s0 = wave_sum(active ? (l1 ? trx : tr - trx) : 0.0);
-        const double s1 = wave_sum(active ? (l1 ? tr - trx : trx) : 0.0);
-        if (lane == 0) {
-            part[w][0] = s0;
-            part[w][1] = s1;
+    rebuild_row2(U);
+    Counts n{0, 0};
+    double tr = heatbath<R, HIT1>(
+        U, A, q32, lid, sweep, seed, nhit, active, n, lds.parking(), lane,
+        [&](int k) { return !SIX && k == 2 ? mine : draw_get<R>(lds.draw[k], lane); },
+        [&](int k, R u4sq, bool &made) {
+            if constexpr (HIT1) {
+                made = false;
+                return mine;
+            } else if constexpr (SIX) {
+                made = true;
+                return draw_get<R>(lds.second[k], lane);
+            } else {
+                if (k == 0) __syncthreads();  // the pool is drawn
+                const int slot = pool_slot(u4sq, k, lane);
+                made = slot >= 0;
+                return draw_get<R>(lds.pool, made ? slot : 0);
+            }
+        });
+    if (active) store_own(own, at.here, U);
+    add_counts(n, counters, slot, lane);
+    if constexpr (MEAS) {
+        // S = sum of D_nu over nu < MU
+        if constexpr (MU == 1) tr = retr_mul(U, lds_get<R, 9>(lds.D[0], lane));
+        if constexpr (MU == 2) {
+            M3<R> S = lds_get<R, 9>(lds.D[0], lane);
+            add_to(S, lds_get<R, 9>(lds.D[1], lane));
+            tr = retr_mul(U, S);
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            meas[0] = part[0][0] + part[1][0] + part[2][0];
-            if (g.nlat == 2) meas[1] = part[0][1] + part[1][1] + part[2][1];
+        if constexpr (!CROSS) {
+            tr = wave_sum(active ? tr : 0.0);
+            if (lane == 0) meas[0] = tr;
+        } else {
+            // the lower terms whose base lies in the other layer: each wave
+            // sums its own direction's share Re Tr(U_new X)
+            lds_put<R, 9>(lds.U, lane, U);
+            __syncthreads();
+            double trx = 0.0;
+            if constexpr (MU == 3) trx = retr_mul(U, lds_get<R, 9>(lds.X, lane));
+            cross_share(lds, active, s.layer != 0, tr, trx, 0, lane);
+            __syncthreads();
+            if (lane == 0) {
+                meas[0] = lds.part[0][0] + lds.part[1][0] + lds.part[2][0];
+                if (g.nlat == 2) meas[1] = lds.part[0][1] + lds.part[1][1] + lds.part[2][1];
+            }
         }
     }
 }
 
-template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG>
-__global__ __launch_bounds__(kSplitBlock, kSplitWaves<R>) void k_pass_split(
+template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG, bool SIX>
+__global__ __launch_bounds__(SIX ? 384 : 192, kSplitWaves<R>) void k_pass_split(
     store_t<R> *__restrict__ links, const Geom g, const int par, const R q32, const R w0, const R w1,
     const uint64_t sweep, const uint64_t seed, const int nhit, unsigned long long *__restrict__ counters,
     double *__restrict__ meas)
 {
-    __shared__ SplitLds<R, TWOB> lds;
-    pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG>(links, g, par, pass_tile(par), q32, w0, w1, sweep, seed, nhit,
+    __shared__ PassLds<R, HIT1, DLT, MEAS, TWOB, MU, SIX> lds;
+    pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, SIX>(links, g, par, pass_tile(par), q32, w0, w1, sweep, seed, nhit,
                                                   counters, blockIdx.x % kCounterSlots,
                                                   MEAS ? meas + (size_t)g.nlat * blockIdx.x : nullptr, lds);
 }
@@ -176,16 +269,16 @@ __device__ __forceinline__ int job_of_tile(const BatchJob *__restrict__ jobs, in
 // contiguous stretches of each job's tiles) belongs to the job whose tile range
 // holds t; job j is at sweep index sweep0 + (step - admit_step).  The record
 // of the job is uniform over the workgroup.
-template <int MU, typename R, bool HIT1, bool DLT, bool BIG>
-__global__ __launch_bounds__(kSplitBlock, kSplitWaves<R>) void k_batch_split(const BatchJob *__restrict__ jobs,
+template <int MU, typename R, bool HIT1, bool DLT, bool BIG, bool SIX>
+__global__ __launch_bounds__(SIX ? 384 : 192, kSplitWaves<R>) void k_batch_split(const BatchJob *__restrict__ jobs,
                                                                              const int njobs, const long long step,
                                                                              const int par)
 {
-    __shared__ SplitLds<R, false> lds;
+    __shared__ PassLds<R, HIT1, DLT, false, false, MU, SIX> lds;
     const int t = pass_tile(par);
     const BatchJob J = jobs[job_of_tile(jobs, njobs, t)];
     const int tile = t - J.tile_begin;
-    pass_split<MU, R, HIT1, DLT, false, false, BIG>((store_t<R> *)J.links, J.g, par, tile, sizeof(R) == 8 ? (R)J.q32 : (R)J.q32f,
+    pass_split<MU, R, HIT1, DLT, false, false, BIG, SIX>((store_t<R> *)J.links, J.g, par, tile, sizeof(R) == 8 ? (R)J.q32 : (R)J.q32f,
                                                     R(0), R(0), J.sweep0 + (uint64_t)(step - J.admit_step), J.seed,
                                                     J.nhit, J.counters, tile % kCounterSlots, nullptr, lds);
 }
@@ -198,7 +291,13 @@ template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BI
 {
     const unsigned grid = (unsigned)pass_blocks(a.g, kPassBlock);
     const R q = TWOB ? R(1.5) : q32_of<R>(a.beta0), w0 = R(a.beta0), w1 = R(a.beta1);
-    k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG><<<grid, kSplitBlock, 0, a.stream>>>(
+    if constexpr (!BIG)
+        if (a.six_waves) {
+            k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, true><<<grid, 384, 0, a.stream>>>(
+                (store_t<R> *)a.links, a.g, a.par, q, w0, w1, a.sweep, a.seed, a.nhit, a.counters, a.meas);
+            return;
+        }
+    k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, false><<<grid, 192, 0, a.stream>>>(
         (store_t<R> *)a.links, a.g, a.par, q, w0, w1, a.sweep, a.seed, a.nhit, a.counters, a.meas);
 }
 
@@ -250,7 +349,12 @@ template <typename R> hipError_t launch_pass_r(const PassArgs &a)
 
 template <int MU, typename R, bool HIT1, bool DLT, bool BIG> void launch_batch_one(const BatchArgs &b)
 {
-    k_batch_split<MU, R, HIT1, DLT, BIG><<<b.ntiles, kSplitBlock, 0, b.stream>>>(b.jobs, b.njobs, b.step, b.par);
+    if constexpr (!BIG)
+        if (b.six_waves) {
+            k_batch_split<MU, R, HIT1, DLT, BIG, true><<<b.ntiles, 384, 0, b.stream>>>(b.jobs, b.njobs, b.step, b.par);
+            return;
+        }
+    k_batch_split<MU, R, HIT1, DLT, BIG, false><<<b.ntiles, 192, 0, b.stream>>>(b.jobs, b.njobs, b.step, b.par);
 }
 
 template <int MU, typename R> void launch_batch_mu(const BatchArgs &b)

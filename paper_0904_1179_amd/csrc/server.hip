@@ -276,7 +276,8 @@ su3_status run_sweeps(su3_server *s, int32_t max_sweeps, int32_t *n_active, int3
                         const Group &G = s->groups[gi];
                         if (!G.njobs) continue;
                         const BatchArgs b{G.d_table,     G.njobs,       G.ntiles, s->step, mu, par,
-                                          (gi & 2) == 0, (gi & 1) != 0, G.big,    s->stream};
+                                          (gi & 2) == 0, (gi & 1) != 0, G.big,
+                                          pass_six_waves(gi < 4 ? 64 : 32, (gi & 2) == 0, G.ntiles), s->stream};
                         e = launch_batch(gi < 4 ? 64 : 32, b);
                         if (e != hipSuccess) return hip_fail(e, "batched pass");
                     }

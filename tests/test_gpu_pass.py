@@ -103,3 +103,32 @@ def test_fp32_layer_couplings_against_oracle(hb, L, flip, nhit):
     assert np.median(d) < 1e-5 and np.mean(d < 1e-4) > 0.9
     if nhit == 1:
         assert lat.counters()[1] == ref.counters()[0]
+
+
+@pytest.mark.parametrize("nhit", [1, 2, 4])
+@pytest.mark.parametrize("nlat,precision", [(1, 64), (2, 64), (1, 32), (2, 32)])
+@pytest.mark.parametrize("beta", [0.4, 5.7])  # 0.4: many links miss outside the draws made ahead
+def test_three_waves_per_tile_as_six(hb, nhit, nlat, precision, beta):
+    """Small batches run six waves per tile of 64 links, large ones three; both
+    make the same draws and sums in the same order, so each job's plaquettes
+    and counts have the same bits in a batch of more than 768 tiles as alone."""
+    from paper_0904_1179_amd import serve
+
+    _say(f"three waves nhit={nhit} nlat={nlat} precision={precision} beta={beta}")
+    L = (4, 6, 6, 38)  # 2736 links per pass and layer: 42.75 tiles
+    tiles = -(-nlat * 2736 // 64)
+    njobs = 768 // tiles + 1
+    srv = serve.Server(arena_bytes=512 << 20, max_active=64)
+    ids = [srv.submit(serve.make_job(L, beta, 2, seed=k + 1, precision=precision, nlat=nlat, nhit=nhit))
+           for k in range(njobs)]
+    while True:
+        nactive, nqueued, _ = srv.run(2)
+        if nactive == 0 and nqueued == 0:
+            break
+    for k in {0, njobs // 2, njobs - 1}:
+        r = srv.poll(ids[k])
+        lat = hb.Lattice(L, nlat=nlat, precision=precision, seed=k + 1, nhit=nhit)
+        lat.start(True)
+        lat.sweep(2, beta)
+        assert np.array_equal(np.array(r["plaquette"][:1 + nlat]), lat.plaquette())
+        assert (r["kp_attempts"], r["kp_accepts"]) == lat.counters()[1:]
