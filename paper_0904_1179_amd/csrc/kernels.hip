@@ -11,7 +11,7 @@
 // entry: whole 128-byte lines, fully coalesced vector loads.
 #include <algorithm>
 
-#include "launch.h"
+#include "pass.h"
 
 namespace su3hb {
 
@@ -30,9 +30,6 @@ template <int NB = kBlock> __device__ __forceinline__ double block_sum(double v)
         for (int w = 0; w < NB / 64; ++w) s += wsum[w];
     return s;
 }
-
-// compiler-only memory barrier
-__device__ __forceinline__ void stash_fence() { __asm__ __volatile__("" ::: "memory"); }
 
 // Polyakov loops along direction 3: thread (layer, x0, x1, x2) walks the
 // closed path x3 = 0, 1, ... (2 L3 links when crossing the direction-3
@@ -165,40 +162,76 @@ __global__ __launch_bounds__(kBlock) void k_gauge(store_t<R> *__restrict__ links
 // ---------------------------------------------------------------------------
 // plaquette: sum over sites of Re Tr U_mu(x) U_nu(x+mu) U_mu(x+nu)^+ U_nu(x)^+
 // = Re Tr P Q^+ with P = U_mu(x) U_nu(x+mu), Q = U_nu(x) U_mu(x+nu), in FP64.
-// Grid (nblk, nlat); fixed per-thread order, wave shuffles and a fixed
-// per-block order, so the sum is bitwise reproducible.
 // ---------------------------------------------------------------------------
-// Rows 0 and 1 of a link (row 2 never formed), in FP64.
-template <typename R> __device__ __forceinline__ M3<double> load_rows01(const store_t<R> *block, int n)
+
+// Re Tr P Q^+ of two SU(3) matrices from their rows 0 and 1: with G_ij = p_i .
+// q_j^* for i, j < 2, the third rows' product is conj(det G) (the third row is
+// the conjugate cross product of the first two).
+__device__ __forceinline__ double retr_pq(const M3<double> &P, const M3<double> &Q)
 {
-    M3<double> m;
-    const store_t<R> *p = link_at<R>(block, n);
+    Cx<double> G[2][2];
 #pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const store_t<R> v = p[e * kTile];
-        m.e[e / 3][e % 3] = Cx<double>{(double)v.x, (double)v.y};
-    }
-    return m;
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            G[i][j] = cmul_cn(Q.e[j][0], P.e[i][0]);
+            G[i][j] = cmadd_cn(G[i][j], Q.e[j][1], P.e[i][1]);
+            G[i][j] = cmadd_cn(G[i][j], Q.e[j][2], P.e[i][2]);
+        }
+    double s = G[0][0].re + G[1][1].re;
+    s = fma(G[0][0].re, G[1][1].re, s);
+    s = fma(-G[0][0].im, G[1][1].im, s);
+    s = fma(-G[0][1].re, G[1][0].re, s);
+    return fma(G[0][1].im, G[1][0].im, s);
 }
 
-// Plane (MU, NU) of a site whose own links U (rows 0, 1) are already held:
-// Re Tr P Q^+ with P = U_MU(x) U_NU(x+MU), Q = U_NU(x) U_MU(x+NU), both
-// SU(3) products formed as rows 0, 1 with row 2 rebuilt.
-template <int MU, int NU, typename R, bool DLT>
-__device__ __forceinline__ double plaq_plane_own(const store_t<R> *__restrict__ links, const Geom &g, const int x[4],
-                                                 int layer, int par, const M3<double> *U)
+// rows 0 and 1 of A B (B with its row 2)
+__device__ __forceinline__ M3<double> rows_nn(const M3<double> &A, const M3<double> &B)
 {
-    const int opp = par ^ 1;
-    const M3<double> P = mul_nn_su3(
-        U[MU], convert<double>(load_link12<R>(planes<R>(links, g, NU, opp), nbr_elem<MU, +1, NU, 0, DLT>(g, x, layer))));
-    const M3<double> Q = mul_nn_su3(
-        U[NU], convert<double>(load_link12<R>(planes<R>(links, g, MU, opp), nbr_elem<NU, +1, MU, 0, DLT>(g, x, layer))));
-    double s = 0.0;
+    M3<double> C;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) s += P.e[a][b].re * Q.e[a][b].re + P.e[a][b].im * Q.e[a][b].im;
-    return s;
+        for (int b = 0; b < 3; ++b) {
+            Cx<double> t = cmul(A.e[a][0], B.e[0][b]);
+            t = cmadd(t, A.e[a][1], B.e[1][b]);
+            C.e[a][b] = cmadd(t, A.e[a][2], B.e[2][b]);
+        }
+    return C;
+}
+
+// Rows 0 and 1 of a link in FP64.
+template <typename R, typename O> __device__ __forceinline__ M3<double> rows_of(Block<R> b, O o)
+{
+    M3<R> m;
+    load_rows(m, b, o);
+    M3<double> d;
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e)
+        d.e[e / 3][e % 3] = Cx<double>{(double)m.e[e / 3][e % 3].re, (double)m.e[e / 3][e % 3].im};
+    return d;
+}
+
+// rebuild_row2 with each real entry a sum of four products in one chain of
+// fused multiply-adds: 24 instructions instead of 30, and fewer roundings
+__device__ __forceinline__ void row2_chain(M3<double> &u)
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const Cx<double> a = u.e[0][(k + 1) % 3], b = u.e[1][(k + 2) % 3];
+        const Cx<double> c = u.e[0][(k + 2) % 3], d = u.e[1][(k + 1) % 3];
+        u.e[2][k].re = fma(c.im, d.im, fma(-c.re, d.re, fma(-a.im, b.im, a.re * b.re)));
+        u.e[2][k].im = fma(c.im, d.re, fma(c.re, d.im, fma(-a.im, b.re, -(a.re * b.im))));
+    }
+}
+
+// Plane (mu, nu) of a site: own links Um, Un (rows 0, 1), neighbours Vn =
+// U_nu(x+mu), Vm = U_mu(x+nu).
+__device__ __forceinline__ double plaq_plane(const M3<double> &Um, const M3<double> &Un, M3<double> Vn, M3<double> Vm)
+{
+    row2_chain(Vn);
+    row2_chain(Vm);
+    return retr_pq(rows_nn(Um, Vn), rows_nn(Un, Vm));
 }
 
 // 1 if the stored rows 0 and 1 of u are not finite or not orthonormal within
@@ -218,60 +251,59 @@ __device__ __forceinline__ int link_bad(const M3<double> &u, double tol)
     return ok ? 0 : 1;
 }
 
-// FP32 plaquette: the six planes of the site and the check of its four own
-// links.  The four own links are loaded once and kept, and compiler-only
-// fences between the planes hold the neighbour loads back (two waves per
-// SIMD: 87 instead of 122 us at 32^4).
-template <typename R, bool DLT>
-__device__ __forceinline__ double plaq_site(const store_t<R> *__restrict__ links, const Geom &g, int layer, int par,
-                                           int i, double tol, int &bad)
-{
-    int x[4];
-    site_coords(g, par, i, x);
-    const int n = layer * g.Vh + i;
-    M3<double> U[4];
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-        U[mu] = load_rows01<R>(planes<R>(links, g, mu, par), n);
-        bad += link_bad(U[mu], tol);
-    }
-    double s = plaq_plane_own<0, 1, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    s += plaq_plane_own<0, 2, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    s += plaq_plane_own<1, 2, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    s += plaq_plane_own<0, 3, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    s += plaq_plane_own<1, 3, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    s += plaq_plane_own<2, 3, R, DLT>(links, g, x, layer, par, U);
-    stash_fence();
-    return s;
-}
-
-// Grid (nblk, nlat).  Workgroup b (XCD-remapped) sums the contiguous run of
-// tiles [b T, (b+1) T) of its layer in the pass order; thread v of a tile
-// takes both sites with half-index i(v) (x0 neighbours), so the links of both
-// parities around a domain are read while they are in that XCD's L2.  Fixed
-// per-thread order, wave shuffles and a fixed per-block order: the sum is
-// bitwise reproducible.  partials[l nblk + b]: plaquette sum of workgroup b
-// of layer l; partials[(nlat + l) nblk + b]: its number of failing links.
-template <typename R, bool DLT>
-__global__ __launch_bounds__(kBlock) void k_plaq_partial(const store_t<R> *__restrict__ links, const Geom g,
-                                                         const int tiles_per_block, const double tol,
-                                                         double *__restrict__ partials)
+// Grid (nblk, nlat), four waves per workgroup.  Workgroup b (XCD-remapped) sums
+// the contiguous run of tiles [b T, (b+1) T) of its layer in the pass order; a
+// tile is 64 half-indices, and each parity's 64 sites are taken by two waves:
+// one for the planes of directions 0, 1, 2, one for the three planes with
+// direction 3.  Fixed order per lane, per wave and per workgroup: the sum is
+// bitwise reproducible.  partials[l nblk + b]: plaquette sum of workgroup b of
+// layer l; partials[(nlat + l) nblk + b]: its number of failing links.
+// Half a site per lane needs 160 registers, three waves per SIMD; one lane per
+// FP64 site took 256.  us per call, one lane per site (FP32: two sites) ->
+// this: FP64 8^4 42 -> 30, 16^4 44 -> 34, 20^4 63 -> 50, 24^4 (walk below) 74 -> 66;
+// FP32 16^4 37 -> 33, 32^4 110 -> 106, 40^4 368 -> 245.  It reads each link 4.75
+// times on average and L2 hits are few, so large FP64 lattices walk instead
+// (32^4 185 us here, 161 there).  Keeping the tile's own links in LDS for its
+// waves spilled.
+template <typename R, bool DLT, bool BIG>
+__global__ __launch_bounds__(kBlock, 2) void k_plaq(const store_t<R> *__restrict__ links, const Geom g,
+                                                    const int tiles_per_block, const double tol,
+                                                    double *__restrict__ partials)
 {
     const int layer = DLT ? (int)blockIdx.y : 0;
     const int b = xcd_tile(blockIdx.x, gridDim.x);
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int par = w & 1, opp = par ^ 1;
+    const bool with3 = w >> 1;
     double s = 0.0;
     int bad = 0;
     for (int t = 0; t < tiles_per_block; ++t) {
-        const int v = (b * tiles_per_block + t) * kBlock + threadIdx.x;
-        if (v < g.Vh) {
-            const int i = order_index(g, v);
-            s += plaq_site<R, DLT>(links, g, layer, 0, i, tol, bad);
-            s += plaq_site<R, DLT>(links, g, layer, 1, i, tol, bad);
+        const int v = (b * tiles_per_block + t) * 64 + lane;
+        if (v >= g.Vh) break;
+        Site x;
+        x.layer = layer;
+        x.i = order_site(g, par, v, x.x);
+        const auto at = [&](Step d) { return link_offset<R, BIG>(elem<DLT>(g, x, d)); };
+        const offset_t<BIG> here = link_offset<R, BIG>(DLT && layer ? x.i + g.Vh : x.i);
+        const auto own = [&](int d) { return rows_of<R>(block_of<R>(links, g, d, par), here); };
+        const auto nbr = [&](int d, offset_t<BIG> o) { return rows_of<R>(block_of<R>(links, g, d, opp), o); };
+        const offset_t<BIG> o0 = at(step_of<0, +1>(g, x)), o1 = at(step_of<1, +1>(g, x)), o2 = at(step_of<2, +1>(g, x));
+        if (!with3) {
+            const M3<double> U0 = own(0), U1 = own(1);
+            s += plaq_plane(U0, U1, nbr(1, o0), nbr(0, o1));
+            bad += link_bad(U0, tol) + link_bad(U1, tol);
+            const M3<double> U2 = own(2);
+            s += plaq_plane(U0, U2, nbr(2, o0), nbr(0, o2));
+            bad += link_bad(U2, tol);
+            s += plaq_plane(U1, U2, nbr(2, o1), nbr(1, o2));
+        } else {
+            const offset_t<BIG> o3 = at(step_of<3, +1>(g, x));
+            const M3<double> U3 = own(3);
+            bad += link_bad(U3, tol);
+            s += plaq_plane(own(0), U3, nbr(3, o0), nbr(0, o3));
+            s += plaq_plane(own(1), U3, nbr(3, o1), nbr(1, o3));
+            s += plaq_plane(own(2), U3, nbr(3, o2), nbr(2, o3));
         }
     }
     const double bs = block_sum(s);
@@ -283,85 +315,32 @@ __global__ __launch_bounds__(kBlock) void k_plaq_partial(const store_t<R> *__res
     }
 }
 
-// FP64 plaquette, one site per thread: thread w of a tile takes the site with
-// half-index i(w / 2) and parity w % 2, so the two threads of a half-index
-// read the two parity blocks at the same element.  The six planes (mu, nu)
-// each load their four links and form P and Q as SU(3) products (rows 0, 1,
-// row 2 rebuilt).  At 32^4: 168 us against 225 us for two sites per thread,
-// which needs 256 VGPRs plus 123 AGPRs (one wave per SIMD).  (Fencing the
-// planes to cut registers further pins every temporary and spills.)  FP32
-// keeps k_plaq_partial, whose fenced planes with held own links take 86 us
-// against 120 us.
-template <int MU, int NU, typename R, bool DLT>
-__device__ __forceinline__ double plaq_plane_su3(const store_t<R> *__restrict__ links, const Geom &g, const int x[4],
-                                                 int layer, int par, int n)
+// Rows 0 and 1 of a link (row 2 never formed), in FP64.
+template <typename R> __device__ __forceinline__ M3<double> load_rows01(const store_t<R> *block, int n)
 {
-    const int opp = par ^ 1;
-    const M3<double> P = mul_nn_su3(
-        convert<double>(load_link12<R>(planes<R>(links, g, MU, par), n)),
-        convert<double>(load_link12<R>(planes<R>(links, g, NU, opp), nbr_elem<MU, +1, NU, 0, DLT>(g, x, layer))));
-    const M3<double> Q = mul_nn_su3(
-        convert<double>(load_link12<R>(planes<R>(links, g, NU, par), n)),
-        convert<double>(load_link12<R>(planes<R>(links, g, MU, opp), nbr_elem<NU, +1, MU, 0, DLT>(g, x, layer))));
-    double s = 0.0;
+    M3<double> m;
+    const store_t<R> *p = link_at<R>(block, n);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) s += P.e[a][b].re * Q.e[a][b].re + P.e[a][b].im * Q.e[a][b].im;
-    return s;
-}
-
-template <typename R, bool DLT>
-__device__ __forceinline__ double plaq_site1(const store_t<R> *__restrict__ links, const Geom &g, int layer,
-                                            int par, int i, double tol, int &bad)
-{
-    int x[4];
-    site_coords(g, par, i, x);
-    const int n = layer * g.Vh + i;
-    double s = plaq_plane_su3<0, 1, R, DLT>(links, g, x, layer, par, n);
-    s += plaq_plane_su3<0, 2, R, DLT>(links, g, x, layer, par, n);
-    s += plaq_plane_su3<1, 2, R, DLT>(links, g, x, layer, par, n);
-    s += plaq_plane_su3<0, 3, R, DLT>(links, g, x, layer, par, n);
-    s += plaq_plane_su3<1, 3, R, DLT>(links, g, x, layer, par, n);
-    s += plaq_plane_su3<2, 3, R, DLT>(links, g, x, layer, par, n);
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu) bad += link_bad(load_rows01<R>(planes<R>(links, g, mu, par), n), tol);
-    return s;
-}
-
-template <typename R, bool DLT>
-__global__ __launch_bounds__(kBlock, 2) void k_plaq_sites(const store_t<R> *__restrict__ links,
-                                                                       const Geom g, const int tiles_per_block,
-                                                                       const double tol, double *__restrict__ partials)
-{
-    const int layer = DLT ? (int)blockIdx.y : 0;
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
-    double s = 0.0;
-    int bad = 0;
-    for (int t = 0; t < tiles_per_block; ++t) {
-        const int w = (b * tiles_per_block + t) * kBlock + threadIdx.x;
-        if (w < 2 * g.Vh) s += plaq_site1<R, DLT>(links, g, layer, w & 1, order_index(g, w >> 1), tol, bad);
+    for (int e = 0; e < 6; ++e) {
+        const store_t<R> v = p[e * kTile];
+        m.e[e / 3][e % 3] = Cx<double>{(double)v.x, (double)v.y};
     }
-    const double bs = block_sum(s);
-    __syncthreads();
-    const double bb = block_sum((double)bad);
-    if (threadIdx.x == 0) {
-        partials[blockIdx.y * gridDim.x + blockIdx.x] = bs;
-        partials[(gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = bb;
-    }
+    return m;
 }
 
-// Re Tr P Q^+ of two SU(3) matrices given by rows 0 and 1 (row 2 rebuilt).
-__device__ __forceinline__ double retr_pq12(M3<double> P, M3<double> Q)
+// rows 0 and 1 of A^+ B (both with row 2)
+__device__ __forceinline__ M3<double> rows_dn(const M3<double> &A, const M3<double> &B)
 {
-    rebuild_row2(P);
-    rebuild_row2(Q);
-    double s = 0.0;
+    M3<double> C;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) s += P.e[a][b].re * Q.e[a][b].re + P.e[a][b].im * Q.e[a][b].im;
-    return s;
+        for (int b = 0; b < 3; ++b) {
+            Cx<double> t = cmul_cn(A.e[0][a], B.e[0][b]);
+            t = cmadd_cn(t, A.e[1][a], B.e[1][b]);
+            C.e[a][b] = cmadd_cn(t, A.e[2][a], B.e[2][b]);
+        }
+    return C;
 }
 
 // One column of the plaquette walk: the sites (x0, x1, x2, x3) of the
@@ -397,41 +376,42 @@ __device__ __forceinline__ double plaq_column(const store_t<R> *__restrict__ lin
         bad += link_bad(U0, tol) + link_bad(U1, tol) + link_bad(U2, tol) + link_bad(U3, tol);
         if (x3 > x3a) {
             // planes (mu, 3) of the site below
-            s += retr_pq12(M0, U0);
-            s += retr_pq12(M1, U1);
-            s += retr_pq12(M2, U2);
+            s += retr_pq(M0, U0);
+            s += retr_pq(M1, U1);
+            s += retr_pq(M2, U2);
         }
         const int e0 = nbr_elem<0, +1, 0, 0, DLT>(g, x, layer);
         const int e1 = nbr_elem<1, +1, 0, 0, DLT>(g, x, layer);
         const int e2 = nbr_elem<2, +1, 0, 0, DLT>(g, x, layer);
         rebuild_row2(U3);
-        s += retr_pq12(mul_nn_su3(U0, convert<double>(load_link12<R>(planes<R>(links, g, 1, opp), e0))),
-                       mul_nn_su3(U1, convert<double>(load_link12<R>(planes<R>(links, g, 0, opp), e1))));
-        s += retr_pq12(mul_nn_su3(U0, convert<double>(load_link12<R>(planes<R>(links, g, 2, opp), e0))),
-                       mul_nn_su3(U2, convert<double>(load_link12<R>(planes<R>(links, g, 0, opp), e2))));
-        M0 = mul_dn_su3(U3, mul_nn_su3(U0, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e0))));
-        s += retr_pq12(mul_nn_su3(U1, convert<double>(load_link12<R>(planes<R>(links, g, 2, opp), e1))),
-                       mul_nn_su3(U2, convert<double>(load_link12<R>(planes<R>(links, g, 1, opp), e2))));
-        M1 = mul_dn_su3(U3, mul_nn_su3(U1, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e1))));
-        M2 = mul_dn_su3(U3, mul_nn_su3(U2, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e2))));
+        s += retr_pq(rows_nn(U0, convert<double>(load_link12<R>(planes<R>(links, g, 1, opp), e0))),
+                       rows_nn(U1, convert<double>(load_link12<R>(planes<R>(links, g, 0, opp), e1))));
+        s += retr_pq(rows_nn(U0, convert<double>(load_link12<R>(planes<R>(links, g, 2, opp), e0))),
+                       rows_nn(U2, convert<double>(load_link12<R>(planes<R>(links, g, 0, opp), e2))));
+        M0 = rows_dn(U3, mul_nn_su3(U0, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e0))));
+        s += retr_pq(rows_nn(U1, convert<double>(load_link12<R>(planes<R>(links, g, 2, opp), e1))),
+                       rows_nn(U2, convert<double>(load_link12<R>(planes<R>(links, g, 1, opp), e2))));
+        M1 = rows_dn(U3, mul_nn_su3(U1, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e1))));
+        M2 = rows_dn(U3, mul_nn_su3(U2, convert<double>(load_link12<R>(planes<R>(links, g, 3, opp), e2))));
     }
     if (x3b > x3a) {
         // planes (mu, 3) of the chunk's last site: the links of the slab above
         x[3] = x3b - 1;
         const int opp = ((x[0] + x[1] + x[2] + x[3]) & 1) ^ 1;
         const int e3 = nbr_elem<3, +1, 0, 0, DLT>(g, x, layer);
-        s += retr_pq12(M0, load_rows01<R>(planes<R>(links, g, 0, opp), e3));
-        s += retr_pq12(M1, load_rows01<R>(planes<R>(links, g, 1, opp), e3));
-        s += retr_pq12(M2, load_rows01<R>(planes<R>(links, g, 2, opp), e3));
+        s += retr_pq(M0, load_rows01<R>(planes<R>(links, g, 0, opp), e3));
+        s += retr_pq(M1, load_rows01<R>(planes<R>(links, g, 1, opp), e3));
+        s += retr_pq(M2, load_rows01<R>(planes<R>(links, g, 2, opp), e3));
     }
     return s;
 }
 
 // Plaquette of large FP64 lattices by walking x3: grid (nblk, nlat),
 // workgroup b (XCD-remapped) takes the threads [b T, (b+1) T) of the column
-// order (walk_column), T = tiles_per_block kPlaqWalkBlock.  Output as
-// k_plaq_partial.  At 32^4 (4 chunks of 8, two waves per SIMD): 143 us
-// against 166 us for one site per thread; at 24^4 53 against 70 us.
+// order (walk_column), T = tiles_per_block kPlaqWalkBlock.  Output as k_plaq.
+// Each link comes from HBM once and its reuse along x3 from registers: a call
+// at 32^4 (4 chunks of 8, two waves per SIMD) takes 161 us against 185 us by
+// tiles, at 64^4 1.93 against 3.6 ms.
 template <typename R, bool DLT>
 __global__ __launch_bounds__(kPlaqWalkBlock, 2) void k_plaq_walk(const store_t<R> *__restrict__ links, const Geom g,
                                                                  const int nch, const int tiles_per_block,
@@ -455,49 +435,43 @@ __global__ __launch_bounds__(kPlaqWalkBlock, 2) void k_plaq_walk(const store_t<R
     }
 }
 
-// Double-layered torus: per-layer plaquette sums of a measured sweep from the
-// nmeas pairs (layer 0, layer 1) of the three measured passes, fixed order:
-// sums[1 + l] = the sum of layer l, sums[0] = sums[1] + sums[2].
-__global__ __launch_bounds__(kBlock) void k_measure_final_dlt(const double *__restrict__ meas, int nmeas,
-                                                              double *__restrict__ sums)
-{
-    double t0 = 0.0, t1 = 0.0;
-    for (int k = threadIdx.x; k < nmeas; k += kBlock) {
-        t0 += meas[2 * k];
-        t1 += meas[2 * k + 1];
-    }
-    const double T0 = block_sum(t0);
-    __syncthreads();
-    const double T1 = block_sum(t1);
-    if (threadIdx.x == 0) {
-        sums[0] = T0 + T1;
-        sums[1] = T0;
-        sums[2] = T1;
-    }
-}
-
 // sums[1 + l] = sum over the partials of layer l; sums[0] = sum over layers;
 // sums[3] = number of links that failed the unitarity check.  With `mean`
 // non-null also the normalised values: mean[0] = sums[0] / (norm nlat),
 // mean[1 + l] = sums[1 + l] / norm, mean[1 + nlat] = sums[3] (norm = 18 V).
-__global__ __launch_bounds__(kBlock) void k_plaq_final(const double *__restrict__ partials, int nblk, int nlat,
-                                                       double *__restrict__ sums, double *__restrict__ mean,
-                                                       double norm)
+// One workgroup of 1024 threads with four loads in flight each: 4096 partials in
+// 5 us (13 us with 256 threads and one load).
+constexpr int kSumBlock = 1024;
+__device__ __forceinline__ double sum_range(const double *__restrict__ a, int n)
+{
+    double s = 0.0;
+    int b = threadIdx.x;
+    for (; b + 3 * kSumBlock < n; b += 4 * kSumBlock) {
+        const double v0 = a[b], v1 = a[b + kSumBlock], v2 = a[b + 2 * kSumBlock], v3 = a[b + 3 * kSumBlock];
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; b < n; b += kSumBlock) s += a[b];
+    return s;
+}
+__global__ __launch_bounds__(kSumBlock) void k_plaq_final(const double *__restrict__ partials, int nblk, int nlat,
+                                                          double *__restrict__ sums, double *__restrict__ mean,
+                                                          double norm)
 {
     double tot = 0.0;
+    const double s0 = sum_range(partials, nblk), s1 = nlat == 2 ? sum_range(partials + nblk, nblk) : 0.0;
+    const double nb = sum_range(partials + nlat * nblk, nlat * nblk);
     for (int l = 0; l < nlat; ++l) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kBlock) s += partials[l * nblk + b];
-        const double r = block_sum(s);
+        const double r = block_sum<kSumBlock>(l == 0 ? s0 : s1);
         __syncthreads();
         if (threadIdx.x == 0) {
             sums[1 + l] = r;
             tot += r;
         }
     }
-    double nb = 0.0;
-    for (int b = threadIdx.x; b < nlat * nblk; b += kBlock) nb += partials[nlat * nblk + b];
-    const double r = block_sum(nb);
+    const double r = block_sum<kSumBlock>(nb);
     if (threadIdx.x == 0) {
         sums[0] = tot;
         if (nlat == 1) sums[2] = 0.0;
@@ -510,8 +484,28 @@ __global__ __launch_bounds__(kBlock) void k_plaq_final(const double *__restrict_
     }
 }
 
+// Double-layered torus: per-layer plaquette sums of a measured sweep from the
+// nmeas pairs (layer 0, layer 1) of the three measured passes, fixed order:
+// sums[1 + l] = the sum of layer l, sums[0] = sums[1] + sums[2].
+__global__ __launch_bounds__(kSumBlock) void k_measure_final_dlt(const double *__restrict__ meas, int nmeas,
+                                                              double *__restrict__ sums)
+{
+    double t0 = 0.0, t1 = 0.0;
+    for (int k = threadIdx.x; k < nmeas; k += kSumBlock) {
+        t0 += meas[2 * k];
+        t1 += meas[2 * k + 1];
+    }
+    const double T0 = block_sum<kSumBlock>(t0);
+    __syncthreads();
+    const double T1 = block_sum<kSumBlock>(t1);
+    if (threadIdx.x == 0) {
+        sums[0] = T0 + T1;
+        sums[1] = T0;
+        sums[2] = T1;
+    }
+}
+
 // single torus: sums[0] = sums[1] = sum of the partials a[0..na), fixed order
-constexpr int kSumBlock = 1024;
 __global__ __launch_bounds__(kSumBlock) void k_sum_partials(const double *__restrict__ a, int na,
                                                             double *__restrict__ sums)
 {
@@ -569,15 +563,26 @@ hipError_t launch_measure_final(const double *meas, const Geom &g, double *sums,
     if (g.nlat == 1)
         k_sum_partials<<<1, kSumBlock, 0, s>>>(meas, nmeas, sums);
     else
-        k_measure_final_dlt<<<1, kBlock, 0, s>>>(meas, nmeas, sums);
+        k_measure_final_dlt<<<1, kSumBlock, 0, s>>>(meas, nmeas, sums);
     return hipGetLastError();
+}
+
+template <typename R>
+static void plaq_launch(const store_t<R> *links, const Geom &g, int nblk, int tpb, double tol, bool big,
+                        double *partials, hipStream_t s)
+{
+    const dim3 grid(nblk, g.nlat);
+    if (big)
+        k_plaq<R, true, true><<<grid, kBlock, 0, s>>>(links, g, tpb, tol, partials);
+    else if (g.nlat == 2)
+        k_plaq<R, true, false><<<grid, kBlock, 0, s>>>(links, g, tpb, tol, partials);
+    else
+        k_plaq<R, false, false><<<grid, kBlock, 0, s>>>(links, g, tpb, tol, partials);
 }
 
 hipError_t launch_plaquette(int precision, const void *links, const Geom &g, double *partials, double *sums,
                             hipStream_t s, double *mean)
 {
-    const bool dlt = g.nlat == 2;
-    const double tol = unitarity_tol(precision);
     const int nch = plaq_walk_chunks(g, precision);
     if (nch > 0) {
         // FP64 lattices with enough columns: the x3 walk
@@ -585,35 +590,25 @@ hipError_t launch_plaquette(int precision, const void *links, const Geom &g, dou
         const dim3 grid(nblk, g.nlat);
         const long long tiles = ((long long)g.L[0] * g.L[1] * g.L[2] * nch + kPlaqWalkBlock - 1) / kPlaqWalkBlock;
         const int tpb = (int)((tiles + nblk - 1) / nblk);
-        if (dlt)
+        const double tol = unitarity_tol(precision);
+        if (g.nlat == 2)
             k_plaq_walk<double, true><<<grid, kPlaqWalkBlock, 0, s>>>((const double2 *)links, g, nch, tpb, tol,
                                                                       partials);
         else
             k_plaq_walk<double, false><<<grid, kPlaqWalkBlock, 0, s>>>((const double2 *)links, g, nch, tpb, tol,
                                                                        partials);
-        k_plaq_final<<<1, kBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
+        k_plaq_final<<<1, kSumBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
         return hipGetLastError();
     }
     const int nblk = plaq_blocks(g);
-    const dim3 grid(nblk, g.nlat);
-    if (precision == 64) {
-        // one site per thread: tiles of kBlock sites
-        const long long tiles = (2LL * g.Vh + kBlock - 1) / kBlock;
-        const int tpb = (int)((tiles + nblk - 1) / nblk);
-        if (dlt)
-            k_plaq_sites<double, true><<<grid, kBlock, 0, s>>>((const double2 *)links, g, tpb, tol, partials);
-        else
-            k_plaq_sites<double, false><<<grid, kBlock, 0, s>>>((const double2 *)links, g, tpb, tol, partials);
-    } else {
-        // two sites (one half-index) per thread
-        const long long tiles = ((long long)g.Vh + kBlock - 1) / kBlock;
-        const int tpb = (int)((tiles + nblk - 1) / nblk);
-        if (dlt)
-            k_plaq_partial<float, true><<<grid, kBlock, 0, s>>>((const float2 *)links, g, tpb, tol, partials);
-        else
-            k_plaq_partial<float, false><<<grid, kBlock, 0, s>>>((const float2 *)links, g, tpb, tol, partials);
-    }
-    k_plaq_final<<<1, kBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
+    const long long tiles = ((long long)g.Vh + 63) / 64;
+    const int tpb = (int)((tiles + nblk - 1) / nblk);
+    const double tol = unitarity_tol(precision);
+    if (precision == 64)
+        plaq_launch<double>((const double2 *)links, g, nblk, tpb, tol, pass_big(g, 64), partials, s);
+    else
+        plaq_launch<float>((const float2 *)links, g, nblk, tpb, tol, pass_big(g, 32), partials, s);
+    k_plaq_final<<<1, kSumBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
     return hipGetLastError();
 }
 

@@ -142,34 +142,37 @@ bool pass_big(const Geom &g, int precision)
 // pass with few tiles waits for; with more tiles than run at once only the
 // number of instructions and the waves per SIMD count, and six waves hold
 // their registers until the slowest ends.  us per pass, six against three waves:
-//   FP64          256 tiles 6.5 / 7.2, 512 8.5 / 9.2, 576 11.4 / 10.9 (two
-//                 workgroups of 128 registers per CU fill 256 CUs at 512);
-//   FP64, 3 hits  256 tiles 10.0 / 11.2, 384 13.7 / 13.1 (six waves make every
-//                 second draw, three only the likely ones);
+//   FP64          256 tiles 6.8 / 7.4, 320 9.7 / 9.1 (a second workgroup of six
+//                 waves of 152 registers does not fit a CU beside the first);
+//   FP64, 3 hits  256 tiles 10.5 / 11.5, 320 13.1 / 13.0;
 //   FP32          768 tiles 8.3 / 8.6, 1024 9.6 / 9.5;
-//   FP32, 3 hits  512 tiles 9.8 / 11.0, 576 11.6 / 11.4.
+//   FP32, 3 hits  512 tiles 9.8 / 11.0, 576 11.6 / 11.4 (six waves make every
+//                 second draw, three only the likely ones).
 bool pass_six_waves(int precision, bool hit1, long long tiles)
 {
-    return tiles <= (precision == 64 ? (hit1 ? 512 : 256) : (hit1 ? 768 : 512));
+    return tiles <= (precision == 64 ? 256 : hit1 ? 768 : 512);
 }
 
 int pass_links_per_block(const Geom &, int) { return kPassBlock; }
 
 int pass_blocks(const Geom &g, int nb) { return (int)ceil_div((long long)g.nlat * g.Vh, nb); }
 
-int plaq_blocks(const Geom &g)
-{
-    const long long need = ceil_div(g.Vh, kBlock);
-    return (int)(need < kPlaqBlocksMax ? need : kPlaqBlocksMax);
-}
+// Workgroups for n tiles, at most `most`, each with the same number of tiles
+// but the last: the XCDs take contiguous runs of workgroups, so empty ones at
+// the end would leave whole XCDs idle (8 x 38 x 56 x 34 in FP32, 4522 tiles: 116 us
+// with 4096 workgroups of up to two tiles).
+static int even_blocks(long long n, int most) { return (int)ceil_div(n, ceil_div(n, most)); }
+
+int plaq_blocks(const Geom &g) { return even_blocks(ceil_div(g.Vh, 64), kPlaqBlocksMax); }
 
 // The plaquette walk (one thread per column and chunk of x3, which reads
 // each link as an own link and as a neighbour in the same step of the walk)
-// takes FP64 lattices with enough columns for one wave per SIMD (65536
-// threads on the 1024 SIMDs) in chunks of at least kPlaqWalkMinSteps sites,
-// aiming at two waves per SIMD (kPlaqWalkThreads).  Smaller lattices, and
-// FP32 links (k_plaq_partial, faster there), take the per-site kernels.
-constexpr long long kPlaqWalkThreads = 131072, kPlaqWalkMinThreads = 65536, kPlaqWalkMinSteps = 4;
+// takes FP64 lattices with enough columns for two waves per SIMD
+// (kPlaqWalkThreads) in chunks of at least kPlaqWalkMinSteps sites: 32^4 161 us
+// against 185 us by tiles, 64^4 1.93 against 3.6 ms.  Smaller ones, which fit
+// the memory-side cache, are faster by tiles (24^4, 1.3 waves per SIMD: 66
+// against 72 us), and so is FP32 (32^4 106 us, 64^4 1.49 ms).
+constexpr long long kPlaqWalkThreads = 131072, kPlaqWalkMinSteps = 4;
 
 int plaq_walk_chunks(const Geom &g, int precision)
 {
@@ -177,23 +180,28 @@ int plaq_walk_chunks(const Geom &g, int precision)
     const long long cols = (long long)g.nlat * g.L[0] * g.L[1] * g.L[2];
     long long nch = ceil_div(kPlaqWalkThreads, cols);
     if (nch > g.L[3] / kPlaqWalkMinSteps) nch = g.L[3] / kPlaqWalkMinSteps;
-    return nch >= 1 && cols * nch >= kPlaqWalkMinThreads ? (int)nch : 0;
+    return nch >= 1 && cols * nch >= kPlaqWalkThreads ? (int)nch : 0;
 }
 
 int plaq_walk_blocks(const Geom &g, int nch)
 {
-    const long long need = ceil_div((long long)g.L[0] * g.L[1] * g.L[2] * nch, kPlaqWalkBlock);
-    const int most = plaq_blocks(g);
-    return (int)(need < most ? need : most);
+    return even_blocks(ceil_div((long long)g.L[0] * g.L[1] * g.L[2] * nch, kPlaqWalkBlock), plaq_blocks(g));
 }
 
 int meas_blocks(const Geom &g, int lanes) { return pass_blocks(g, pass_links_per_block(g, lanes)); }
 
 int polyakov_blocks(const Geom &g) { return (int)ceil_div((long long)g.L[0] * g.L[1] * g.L[2], kBlock); }
 
-// plaquette partials: per layer and workgroup the plaquette sum, then the
-// number of links that fail the unitarity check
-size_t meas_offset(const Geom &g) { return (size_t)round_up(kOffPartials + 2 * 8LL * g.nlat * plaq_blocks(g), 256); }
+// Plaquette partials: per layer and workgroup the plaquette sum, then the
+// number of links that fail the unitarity check.  They begin at kOffPartials
+// and may run on into the measured-pass partials, 24 nlat bytes or more per 64
+// half-indices: either region is written and summed up within one call, in
+// stream order, and holds nothing between calls.
+size_t meas_offset(const Geom &g)
+{
+    const long long slots = ceil_div(g.Vh, kBlock);
+    return (size_t)round_up(kOffPartials + 2 * 8LL * g.nlat * (slots < kPlaqBlocksMax ? slots : kPlaqBlocksMax), 256);
+}
 
 // measured-pass partials: 3 passes x nlat doubles per workgroup
 size_t polyakov_offset(const Geom &g)

@@ -132,3 +132,26 @@ def test_three_waves_per_tile_as_six(hb, nhit, nlat, precision, beta):
         lat.sweep(2, beta)
         assert np.array_equal(np.array(r["plaquette"][:1 + nlat]), lat.plaquette())
         assert (r["kp_attempts"], r["kp_accepts"]) == lat.counters()[1:]
+
+
+@pytest.mark.parametrize("L,nlat,flip,precision", [
+    ((2, 2, 2, 2), 1, None, 64),          # 8 of the 64 half-indices of a tile
+    ((4, 4, 4, 2), 2, 0xF, 64),           # exactly one tile
+    ((6, 4, 10, 2), 2, 0x5, 32),          # 240: a partial last tile
+    ((66, 4, 2, 4), 1, None, 64),         # 1056
+    ((32, 32, 32, 12), 1, None, 64),      # 98304 columns and chunks: tiles
+    ((32, 32, 32, 16), 1, None, 64),      # 131072: the walk
+])
+def test_plaquette_tiles_and_walk(hb, L, nlat, flip, precision):
+    """Hot lattices against the oracle.  Each of the terms, at most 1 in
+    magnitude, takes some 60 roundings of 1.1e-16, and the partial sums of a
+    hot lattice stay small: below 1e-13.  FP32 holds links rounded to 6e-8,
+    whose errors average out over the plaquettes: below 1e-7."""
+    from oracle import su3ref
+
+    _say(f"plaquette L={L} nlat={nlat} flip={flip} precision={precision}")
+    lat = hb.Lattice(L, nlat=nlat, flip_mask=flip, precision=precision, seed=9)
+    ref = su3ref.Oracle(L, nlat=nlat, flip_mask=flip, seed=9)
+    lat.start(True)
+    ref.start(True)
+    assert np.abs(lat.plaquette() - ref.plaquette()).max() < (1e-13 if precision == 64 else 1e-7)
