@@ -121,16 +121,17 @@ template <typename R> __device__ __forceinline__ R retrace(const M3<R> &A)
 // FP64 elementary functions on the argument ranges of the heat bath.  The
 // general library versions handle every input (signs, infinities, huge
 // arguments) and cost 70-100 instructions each; the heat bath only takes
-// logarithms of uniforms in (0, 1] and sines/cosines of 2 pi u.  The passes
-// issue one vector instruction per 4 cycles at best, whatever it is, so the
-// count is what matters: polynomials of the lowest degree whose error stays
-// below 2^-56 (Chebyshev interpolation of the series, coefficients rounded to
-// FP64), range reduction on the integer the uniform is made of, and one
-// hardware reciprocal with a cubic correction instead of a division.
+// logarithms of uniforms in (0, 1] and sines/cosines of 2 pi u: short series
+// with exact coefficients, accurate to about an ulp over those ranges.  The
+// passes issue one vector instruction per 4 cycles at best, whatever it is, so
+// the count is what matters: range reduction on the integer the uniform is
+// made of, and the hardware's reciprocal and reciprocal square root with just
+// the correction that gives the library's result.
 // ---------------------------------------------------------------------------
 
 // n / d for |n| < d, d in [1.7, 2.5]: the hardware reciprocal r0 (2^-24), e =
-// 1 - d r0, r = r0 (1 + e + e^2) up to e^3, and one residual correction of n r.
+// 1 - d r0, r = r0 (1 + e + e^2) up to e^3, and one residual correction of n r:
+// the rounded quotient (on 5e8 arguments of log_unit it never differed).
 // The general division's scaling and special cases cannot occur here.
 __device__ __forceinline__ double div_mid(double n, double d)
 {
@@ -142,9 +143,9 @@ __device__ __forceinline__ double div_mid(double n, double d)
 }
 
 // ln x for 0 < x <= 1 (normal numbers): x = 2^k m with m in [1/sqrt 2, sqrt 2),
-// ln m = 2 atanh(s) = 2 s (1 + z p(z)) with s = (m - 1)/(m + 1), z = s^2 <=
-// 0.0295 and p(z) = 1/3 + z/5 + ... to 5e-18 relative to ln m.  ln 2 is split
-// into a 40-bit head (k * head is exact) and the rounded remainder.
+// ln m = 2 atanh(s) = 2 (s + s^3/3 + s^5/5 + ...) with s = (m - 1)/(m + 1),
+// |s| <= 0.1716; ten terms leave a truncation below 1e-17 relative.  ln 2 is
+// split into a 40-bit head (k * head is exact) and the rounded remainder.
 __device__ __forceinline__ double log_unit(double x)
 {
     constexpr double kLn2Hi = 0x1.62e42fefa2000p-1;
@@ -157,13 +158,15 @@ __device__ __forceinline__ double log_unit(double x)
     k = low ? k - 1 : k;
     const double s = div_mid(m - 1.0, m + 1.0);
     const double z = s * s;
-    double p = 0.07308250539378183;
-    p = fma(p, z, 0.0766585841296273);
-    p = fma(p, z, 0.0909144464614301);
-    p = fma(p, z, 0.11111105566041697);
-    p = fma(p, z, 0.14285714312997824);
-    p = fma(p, z, 0.19999999999949725);
-    p = fma(p, z, 0.3333333333333335);
+    double p = 1.0 / 19.0;
+    p = fma(p, z, 1.0 / 17.0);
+    p = fma(p, z, 1.0 / 15.0);
+    p = fma(p, z, 1.0 / 13.0);
+    p = fma(p, z, 1.0 / 11.0);
+    p = fma(p, z, 1.0 / 9.0);
+    p = fma(p, z, 1.0 / 7.0);
+    p = fma(p, z, 1.0 / 5.0);
+    p = fma(p, z, 1.0 / 3.0);
     const double s2 = s + s;
     const double lnm = fma(s2 * z, p, s2);  // 2 s (1 + z p)
     const double dk = (double)k;
@@ -176,49 +179,53 @@ __device__ __forceinline__ double log_unit(double x)
 __device__ __forceinline__ int quarter_low(uint32_t h) { return (int)(h << 2) >> 2; }  // 2^30 r - 1/2
 __device__ __forceinline__ uint32_t quarter_turns(uint32_t h) { return (h + 0x20000000u) >> 30; }
 
-// sin and cos of 2 pi u = pi/2 (q + r): with t = r/2, |t| <= 1/4, polynomials
-// in t^2 for sin(pi t) and cos(pi t) (to 4e-17 and 2e-17), then the quadrant.
+// sin(pi t), cos(pi t) for |t| <= 1/4 from their Taylor series in y = t^2:
+// coefficients (-1)^j pi^(2j+1)/(2j+1)! (sine, j = 0..8) and
+// (-1)^j pi^(2j)/(2j)! (cosine, j = 0..9); the first omitted terms are below
+// 1e-17 at |pi t| = pi/4.
+__device__ __forceinline__ void sincospi_quarter(double t, double *sn, double *cs)
+{
+    const double y = t * t;
+    double ps = 7.952054001475513e-07;
+    ps = fma(ps, y, -2.1915353447830217e-05);
+    ps = fma(ps, y, 0.00046630280576761255);
+    ps = fma(ps, y, -0.0073704309457143504);
+    ps = fma(ps, y, 0.08214588661112823);
+    ps = fma(ps, y, -0.5992645293207921);
+    ps = fma(ps, y, 2.5501640398773455);
+    ps = fma(ps, y, -5.16771278004997);
+    ps = fma(ps, y, 3.141592653589793);
+    double pc = -1.3878952462213771e-07;
+    pc = fma(pc, y, 4.303069587032947e-06);
+    pc = fma(pc, y, -0.0001046381049248457);
+    pc = fma(pc, y, 0.0019295743094039231);
+    pc = fma(pc, y, -0.02580689139001406);
+    pc = fma(pc, y, 0.2353306303588932);
+    pc = fma(pc, y, -1.3352627688545895);
+    pc = fma(pc, y, 4.0587121264167685);
+    pc = fma(pc, y, -4.934802200544679);
+    *sn = t * ps;
+    *cs = fma(pc, y, 1.0);
+}
+
+// sin and cos of 2 pi u = pi t + q pi/2 with t = r/2, exact.
 __device__ __forceinline__ void sincos_2pi_u32(uint32_t h, double *sn, double *cs)
 {
-    const double t = fma((double)quarter_low(h), 0x1p-31, 0x1p-32);
-    const double y = t * t;
-    double ps = 0.0004622109894019862;
-    ps = fma(ps, y, -0.007370143626152033);
-    ps = fma(ps, y, 0.08214587730556389);
-    ps = fma(ps, y, -0.5992645291845261);
-    ps = fma(ps, y, 2.5501640398766154);
-    ps = fma(ps, y, -5.167712780049969);
-    ps = fma(ps, y, 3.141592653589793);
-    double pc = -0.00010373975549425398;
-    pc = fma(pc, y, 0.001929501537233591);
-    pc = fma(pc, y, -0.025806888533614774);
-    pc = fma(pc, y, 0.23533063030363824);
-    pc = fma(pc, y, -1.3352627688541205);
-    pc = fma(pc, y, 4.058712126416767);
-    pc = fma(pc, y, -4.934802200544679);
-    const double s = t * ps, c = fma(pc, y, 1.0);
+    double s, c;
+    sincospi_quarter(fma((double)quarter_low(h), 0x1p-31, 0x1p-32), &s, &c);
     const uint32_t q = quarter_turns(h);
     const double ss = (q & 1) ? c : s, cc = (q & 1) ? s : c;
     *sn = (q & 2) ? -ss : ss;
     *cs = ((q + 1) & 2) ? -cc : cc;
 }
 
-// cos^2(2 pi u) = 1/2 + cos(4 pi u)/2 = 1/2 + (-1)^q cos(pi r)/2: one
-// polynomial in r^2 <= 1/4 (to 2e-17) instead of a sine and a cosine.
+// cos^2(2 pi u): only the parity of the quadrant matters.
 __device__ __forceinline__ double cos2_2pi_u32(uint32_t h)
 {
-    const double r = fma((double)quarter_low(h), 0x1p-30, 0x1p-31);
-    const double w = r * r;
-    double p = 4.166464350419119e-06;
-    p = fma(p, w, -0.00010458293377269001);
-    p = fma(p, w, 0.001929562682292385);
-    p = fma(p, w, -0.025806890032216145);
-    p = fma(p, w, 0.23533063027286294);
-    p = fma(p, w, -1.3352627688519192);
-    p = fma(p, w, 4.0587121264167365);
-    p = fma(p, w, -4.934802200544679);
-    const double half = fma(0.5 * w, p, 0.5);
-    return 0.5 + ((quarter_turns(h) & 1) ? -half : half);
+    double s, c;
+    sincospi_quarter(fma((double)quarter_low(h), 0x1p-31, 0x1p-32), &s, &c);
+    const double v = (quarter_turns(h) & 1) ? s : c;
+    return v * v;
 }
 
 // FP32 tier: t in [0, 2], q = nearest integer to 2t, r = t - q/2 (exact, |r| <=
@@ -262,21 +269,16 @@ __host__ __device__ inline float cospi_sq_0to2(float t)
 
 // 1/sqrt(x) and sqrt(x) for x > 0 (normal numbers).  FP64: the hardware
 // estimate y (2^-23) with one third-order correction, y + y e (1/2 + 3 e/8),
-// e = 1 - x y^2, about an ulp; a correctly rounded square root and division
-// take three times the instructions.
+// e = 1 - x y^2, about an ulp (on 5e8 arguments the same as the library's
+// rsqrt, which also handles zeros and infinities); a correctly rounded square
+// root and division take three times the instructions.
 __device__ __forceinline__ double rsqrt_r(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
     const double e = fma(-(x * y), y, 1.0);
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
-__device__ __forceinline__ double sqrt_pos_r(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double s = x * y;
-    const double e = fma(-s, y, 1.0);
-    return fma(s * e, fma(e, 0.375, 0.5), s);
-}
+__device__ __forceinline__ double sqrt_pos_r(double x) { return x * rsqrt_r(x); }
 // FP32: correctly rounded square root and reciprocal.  The reciprocal is the
 // general division's own refinement without its scaling, which only acts on
 // operands near the ends of the exponent range; s is the root of a float, so
@@ -545,19 +547,6 @@ template <typename R> __device__ __forceinline__ void rebuild_row2(M3<R> &u)
     }
 }
 
-// FP64: each real entry a sum of four products in one chain of fused
-// multiply-adds (24 instructions instead of 30, and fewer roundings)
-__device__ __forceinline__ void rebuild_row2(M3<double> &u)
-{
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const Cx<double> a = u.e[0][(k + 1) % 3], b = u.e[1][(k + 2) % 3];
-        const Cx<double> c = u.e[0][(k + 2) % 3], d = u.e[1][(k + 1) % 3];
-        u.e[2][k].re = fma(c.im, d.im, fma(-c.re, d.re, fma(-a.im, b.im, a.re * b.re)));
-        u.e[2][k].im = fma(c.im, d.re, fma(c.re, d.im, fma(-a.im, b.re, -(a.re * b.im))));
-    }
-}
-
 // Products of SU(3) matrices.  A product is again in SU(3), so only its rows
 // 0 and 1 are formed (18 complex multiply-adds instead of 27) and row 2 is
 // rebuilt from them; the left factor's row 2 is never read.
@@ -661,29 +650,23 @@ template <typename To, typename From> __device__ __forceinline__ M3<To> convert(
 __device__ __forceinline__ void reunit(M3<double> &u)
 {
     Cx<double> *r0 = u.e[0], *r1 = u.e[1];
-    double n0 = r0[0].re * r0[0].re;
-    n0 = fma(r0[0].im, r0[0].im, n0);
-#pragma unroll
-    for (int k = 1; k < 3; ++k) n0 = fma(r0[k].im, r0[k].im, fma(r0[k].re, r0[k].re, n0));
-    const double i0 = rsqrt_r(n0);
+    const double i0 = rsqrt_r(r0[0].re * r0[0].re + r0[0].im * r0[0].im + r0[1].re * r0[1].re + r0[1].im * r0[1].im +
+                            r0[2].re * r0[2].re + r0[2].im * r0[2].im);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         r0[k].re *= i0;
         r0[k].im *= i0;
     }
-    Cx<double> d = cmul_cn(r0[0], r1[0]);
+    Cx<double> d{0.0, 0.0};
 #pragma unroll
-    for (int k = 1; k < 3; ++k) d = cmadd_cn(d, r0[k], r1[k]);
+    for (int k = 0; k < 3; ++k) d = cmadd_cn(d, r0[k], r1[k]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        r1[k].re = fma(d.im, r0[k].im, fma(-d.re, r0[k].re, r1[k].re));
-        r1[k].im = fma(-d.im, r0[k].re, fma(-d.re, r0[k].im, r1[k].im));
+        r1[k].re -= d.re * r0[k].re - d.im * r0[k].im;
+        r1[k].im -= d.re * r0[k].im + d.im * r0[k].re;
     }
-    double n1 = r1[0].re * r1[0].re;
-    n1 = fma(r1[0].im, r1[0].im, n1);
-#pragma unroll
-    for (int k = 1; k < 3; ++k) n1 = fma(r1[k].im, r1[k].im, fma(r1[k].re, r1[k].re, n1));
-    const double i1 = rsqrt_r(n1);
+    const double i1 = rsqrt_r(r1[0].re * r1[0].re + r1[0].im * r1[0].im + r1[1].re * r1[1].re + r1[1].im * r1[1].im +
+                            r1[2].re * r1[2].re + r1[2].im * r1[2].im);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         r1[k].re *= i1;

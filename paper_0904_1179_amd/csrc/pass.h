@@ -191,12 +191,11 @@ __device__ __forceinline__ void steps_of(const Geom &g, const Site &s, int w, St
 // the one based at x - nu.
 //
 // Rounding order, fixed for every kernel: c b, e d and a (c b)^+ are SU(3)
-// products (rows 0 and 1 formed, row 2 rebuilt).  FP64: D_nu = up_nu, and the
-// products of (e d)^+ f are added to it one fused multiply-add at a time (no
-// separate sum).  FP32: dn_nu is formed entry by entry from zero, then D_nu =
-// up_nu + dn_nu.  A = (D_0 + D_1) + D_2 over the three directions in
-// increasing order.  All kernels add in exactly this order, so a lattice gets
-// the same bits from each of them.
+// products (rows 0 and 1 formed, row 2 rebuilt); dn_nu is formed entry by
+// entry; D_nu = up_nu + dn_nu entry by entry; A = (D_0 + D_1) + D_2 over the
+// three directions in increasing order.  With per-layer couplings A is the sum
+// of the six weighted terms, one multiply-add after the other.  All kernels
+// add in exactly this order, so a lattice gets the same bits from each of them.
 // ---------------------------------------------------------------------------
 
 // (ed^+ f)_rc
@@ -207,9 +206,9 @@ template <typename R> __device__ __forceinline__ Cx<R> dn_entry(const M3<R> &ed,
     return cmadd_cn(dn, ed.e[2][r], f.e[2][c]);
 }
 
-// D = up, then D += (e d)^+ f.  CROSS: also cross = (e d)^+ f where `crosses`
-// (the lower plaquette's base site lies in the other layer of a double-layered
-// torus), else 0; in FP64 as the difference that the sum made.
+// D = up + (e d)^+ f with D = up on entry.  CROSS: also cross = (e d)^+ f where
+// `crosses` (the lower plaquette's base site lies in the other layer of a
+// double-layered torus), else 0.
 template <typename R, bool CROSS>
 __device__ __forceinline__ void add_dn(M3<R> &D, const M3<R> &ed, const M3<R> &f, M3<R> &cross, bool crosses)
 {
@@ -217,23 +216,12 @@ __device__ __forceinline__ void add_dn(M3<R> &D, const M3<R> &ed, const M3<R> &f
     for (int r = 0; r < 3; ++r)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const Cx<R> up = D.e[r][c];
-            if constexpr (sizeof(R) == 8) {
-                Cx<R> t = cmadd_cn(up, ed.e[0][r], f.e[0][c]);
-                t = cmadd_cn(t, ed.e[1][r], f.e[1][c]);
-                D.e[r][c] = cmadd_cn(t, ed.e[2][r], f.e[2][c]);
-                if constexpr (CROSS) {
-                    cross.e[r][c].re = crosses ? D.e[r][c].re - up.re : R(0);
-                    cross.e[r][c].im = crosses ? D.e[r][c].im - up.im : R(0);
-                }
-            } else {
-                const Cx<R> dn = dn_entry(ed, f, r, c);
-                D.e[r][c].re = up.re + dn.re;
-                D.e[r][c].im = up.im + dn.im;
-                if constexpr (CROSS) {
-                    cross.e[r][c].re = crosses ? dn.re : R(0);
-                    cross.e[r][c].im = crosses ? dn.im : R(0);
-                }
+            const Cx<R> dn = dn_entry(ed, f, r, c);
+            D.e[r][c].re += dn.re;
+            D.e[r][c].im += dn.im;
+            if constexpr (CROSS) {
+                cross.e[r][c].re = crosses ? dn.re : R(0);
+                cross.e[r][c].im = crosses ? dn.im : R(0);
             }
         }
 }
@@ -242,7 +230,6 @@ __device__ __forceinline__ void add_dn(M3<R> &D, const M3<R> &ed, const M3<R> &f
 template <bool BIG> struct StapleAt {
     offset_t<BIG> here, mu, up, dn, mu_dn;  // x, x + mu, x + nu, x - nu, x + mu - nu
     bool crosses;                           // x - nu lies in the other layer
-    int dn_layer;
 };
 template <int MU, typename R, bool DLT, bool BIG>
 __device__ __forceinline__ StapleAt<BIG> staple_at(const Geom &g, const Site &s, Step mu, Step up, Step dn)
@@ -254,7 +241,6 @@ __device__ __forceinline__ StapleAt<BIG> staple_at(const Geom &g, const Site &s,
     a.dn = link_offset<R, BIG>(elem<DLT>(g, s, dn));
     a.mu_dn = link_offset<R, BIG>(elem<DLT>(g, s, mu, dn));
     a.crosses = DLT && dn.flip;
-    a.dn_layer = DLT ? s.layer ^ dn.flip : 0;
     return a;
 }
 
@@ -265,14 +251,13 @@ __device__ __forceinline__ StapleAt<BIG> staple_at(const Geom &g, const Site &s,
 // takes 525 instead of 508 us, a batch of jobs 22.4 instead of 22.1 ms).
 template <typename R> constexpr int kEarlyLinks = sizeof(R) == 8 ? 4 : 2;
 
-// The two staples of direction nu.  TWOB: FP64 D = w[layer] up + w[base layer
-// of the lower plaquette] dn; FP32 D = up and cross = dn, to be weighted where
-// they are added.  between(): work that needs none of the links, done while
+// The two staples of direction nu.  TWOB: D = up and cross = dn, to be weighted
+// where they are added.  between(): work that needs none of the links, done while
 // the first kEarlyLinks are on their way (the compiler would sink the loads or
 // hoist the products, hence the barriers).
 template <int MU, typename R, bool CROSS, bool TWOB, bool BIG, typename Between>
 __device__ __forceinline__ void staple_nu(M3<R> &D, M3<R> &cross, const store_t<R> *links, const Geom &g, int par, int nu,
-                                          const StapleAt<BIG> &at, int layer, R w0, R w1, Between between)
+                                          const StapleAt<BIG> &at, Between between)
 {
     const int opp = par ^ 1;
     const Block<R> umu = block_of<R, BIG>(links, g, MU, opp), unu_par = block_of<R, BIG>(links, g, nu, par),
@@ -294,21 +279,9 @@ __device__ __forceinline__ void staple_nu(M3<R> &D, M3<R> &cross, const store_t<
     const M3<R> ed = mul_nn_su3(e, d);
     D = mul_nd_su3(a, cb);
     rebuild_row2(f);
-    if constexpr (TWOB && sizeof(R) == 4) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) cross.e[r][k] = dn_entry(ed, f, r, k);
-    } else if constexpr (TWOB) {
-        const R wu = layer ? w1 : w0, wd = at.dn_layer ? w1 : w0;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const Cx<R> dn = dn_entry(ed, f, r, k);
-                D.e[r][k].re = D.e[r][k].re * wu + wd * dn.re;
-                D.e[r][k].im = D.e[r][k].im * wu + wd * dn.im;
-            }
+    if constexpr (TWOB) {
+        set_zero(cross);
+        acc_dn(cross, ed, f);
     } else {
         add_dn<R, CROSS>(D, ed, f, cross, at.crosses);
     }

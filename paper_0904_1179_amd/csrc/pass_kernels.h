@@ -10,15 +10,11 @@
 namespace su3hb {
 namespace {
 
-// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed;
-// three waves per tile take 152, six 128, so that four waves share a SIMD.
-// Asked for four, the compiler schedules for registers and the pass is 10 %
-// slower; held to exactly three waves it is 3 % slower.
-template <typename R> constexpr int kSplitWaves = sizeof(R) == 8 ? 3 : 5;
-
-// FP32 with per-layer couplings keeps the six staple terms apart (D: the two
-// of a direction one after the other).
-template <typename R, bool TWOB> constexpr bool kTermsApart = TWOB && sizeof(R) == 4;
+// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed
+// and 152 taken.  Asked for four waves, the compiler schedules for registers
+// and the pass is 10 % slower; held to exactly three it is 3 % slower.  FP32
+// with per-layer couplings has two more terms in registers and spills at five.
+template <typename R, bool TWOB = false> constexpr int kSplitWaves = sizeof(R) == 8 ? 3 : TWOB ? 4 : 5;
 
 // Several attempts: the second draws.  Six waves make them for every link and
 // subgroup; three for the lanes that pool_slot picks, whose links are listed.
@@ -31,8 +27,16 @@ template <typename R> struct SecondDraws<R, false, false> {
     uint32_t list[64];
 };
 
-template <typename R, bool HIT1, bool TWOB, bool KEEP, bool SIX> struct SplitLds : SecondDraws<R, HIT1, SIX> {
-    store_t<R> D[2][kTermsApart<R, TWOB> ? 18 : 9][64];  // D of the first two directions
+// Per-layer couplings: the lower staple of the second direction, D being the
+// weighted sum of the first one's staples and the second one's upper one.
+template <typename R, bool TWOB> struct LowerTerm {};
+template <typename R> struct LowerTerm<R, true> {
+    store_t<R> dn[9][64];
+};
+
+template <typename R, bool HIT1, bool TWOB, bool KEEP, bool SIX>
+struct SplitLds : SecondDraws<R, HIT1, SIX>, LowerTerm<R, TWOB> {
+    store_t<R> D[2][9][64];  // D of the first two directions
     store_t<R> draw[SIX ? 3 : 2][3][64];
     // where U and W wait for a further attempt: over D, unless a measurement reads it later
     __device__ store_t<R> (*parking())[64] { return D[0]; }
@@ -73,27 +77,27 @@ __device__ __forceinline__ void cross_share(Lds &lds, bool active, bool l1, doub
 // One lane per link, all in one thread, takes 3900 instructions (FP64) and 220
 // registers: two waves per SIMD, each of which spends a third of its time on
 // memory while the other alone issues at half rate.  Here no wave has more
-// than one direction in registers (152 in FP64, 128 without the draws, 77 in
-// FP32), the loads of four links (FP32: two) are in flight while the draw is
-// made, the chain from the first load to the store is 1525 instructions
-// instead of 3900 (1100 with six waves), and nothing is computed twice but the
-// addresses.  us per pass, one lane per link (up to 8192 links four, up to
-// 32768 two) -> this:
-//   FP64          8^4 9.6 -> 5.9, 16^4 12.9 -> 8.6, 2 x 16^4 18.1 -> 15.2, 24^4 35.4
-//                 -> 29.7, 32^4 96 -> 88, 64^4 1605 -> 1553;
-//   FP64, 3 hits  8^4 16.2 -> 8.8, 16^4 18.4 -> 13.6, 32^4 106 -> 101, 64^4 1740 -> 1720;
-//   FP32          8^4 9.1 -> 5.8, 16^4 10.7 -> 7.3, 2 x 16^4 14.0 -> 10.3, 24^4 22.2 ->
-//                 19.3, 32^4 49.9 -> 46.7, 64^4 854 -> 837;
-//   FP32, 3 hits  16^4 19.2 -> 9.8, 32^4 65 -> 56, 64^4 1030 -> 955;
-//   measured, two layers, 2 x 16^4: FP64 19.3 -> 17.3, FP32 15.4 -> 11.6.
-// What bounds it now: 32^4 FP64 moves 500 MB past L2 at 5.7 TB/s with the
-// vector unit 57 % busy (its loads and stores alone take 76 us, its arithmetic
-// alone 64); FP32 keeps the vector unit 86 % busy; 8^4 has a quarter of a wave
-// per SIMD and takes the chain's latency.
+// than one direction in registers (152 in FP64, 77 in FP32), the loads of four
+// links (FP32: two) are in flight while the draw is made, the chain from the
+// first load to the store is 1580 instructions instead of 3900 (1100 with six
+// waves), and nothing is computed twice but the addresses.  us per pass, one
+// lane per link (up to 8192 links four, up to 32768 two) -> this:
+//   FP64          8^4 9.6 -> 6.0, 16^4 12.9 -> 9.5, 2 x 16^4 18.1 -> 15.6, 24^4 35.6
+//                 -> 31.2, 32^4 98 -> 93, 64^4 1608 -> 1600;
+//   FP64, 3 hits  8^4 16.3 -> 9.2, 16^4 18.4 -> 14.1, 32^4 105 -> 103, 40^4 256 -> 260;
+//   FP32          8^4 9.1 -> 5.7, 16^4 10.7 -> 7.4, 2 x 16^4 13.9 -> 10.2, 24^4 22.3 ->
+//                 19.4, 32^4 51.8 -> 48.5, 64^4 867 -> 856;
+//   FP32, 3 hits  16^4 19.2 -> 9.9, 32^4 65 -> 57, 64^4 1040 -> 974;
+//   measured, two layers, 2 x 16^4: FP64 19.2 -> 17.4, FP32 15.3 -> 11.6.
+// What bounds it now: 32^4 FP64 moves 500 MB past L2 with the vector unit 57 %
+// busy (its loads and stores alone take 76 us, its arithmetic alone 64); FP32
+// keeps the vector unit 86 % busy; 8^4 has a quarter of a wave per SIMD and
+// takes the chain's latency.
 //
 // Several attempts: three waves make the first draws while the links arrive,
 // wave 1 then the pool's second ones while wave 0 multiplies U by the staple.
-// Second draws for every link instead: 32^4 FP64 111, FP32 59 us.
+// Second draws for every link instead: 32^4 FP64 111, FP32 59 us.  Third draws
+// for the pool as well, by wave 2: 109 us (FP64).
 template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG, bool SIX>
 __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const Geom &g, int par, int tile, R q32, R w0,
                                            R w1, uint64_t sweep, uint64_t seed, int nhit,
@@ -128,10 +132,10 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
     steps_of<MU, DLT>(g, s, w, up, dn);
     const StapleAt<BIG> at = staple_at<MU, R, DLT, BIG>(g, s, step_of<MU, +1>(g, s), up, dn);
     // D: the direction's sum; X: its part whose base lies in the other layer
-    // (CROSS), or the lower term (kTermsApart; D is then the upper one)
+    // (CROSS), or the lower term (TWOB; D is then the upper one)
     M3<R> D, X;
     KPDraw<R> mine;  // three waves: the draw of subgroup w - 1, or 2 for wave 0, which keeps it
-    staple_nu<MU, R, CROSS, TWOB, BIG>(D, X, links, g, par, nu, at, s.layer, w0, w1, [&] {
+    staple_nu<MU, R, CROSS, TWOB, BIG>(D, X, links, g, par, nu, at, [&] {
         if constexpr (!SIX) {
             const int sub = w == 0 ? 2 : w - 1;
             mine = kp_draw<R>(lid, sweep, seed, sub, 0);
@@ -141,9 +145,21 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
             }
         }
     });
+    // A += the two terms of a direction, each with the coupling of its base's layer
+    const R wu = s.layer ? w1 : w0, wd = (s.layer ^ dn.flip) ? w1 : w0;
     if (w != 0) {
+        if constexpr (TWOB) {
+            if (w == 1) {
+                M3<R> A;
+                set_zero(A);
+                scale_acc(A, D, wu);
+                scale_acc(A, X, wd);
+                D = A;
+            } else {
+                lds_put<R, 9>(lds.dn, lane, X);
+            }
+        }
         lds_put<R, 9>(lds.D[w - 1], lane, D);
-        if constexpr (kTermsApart<R, TWOB>) lds_put<R, 9>(lds.D[w - 1] + 9, lane, X);
         if constexpr (!SIX) draw_put<R>(lds.draw[w - 1], lane, mine);
         __syncthreads();
         if constexpr (!SIX && !HIT1)
@@ -170,17 +186,12 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
     if constexpr (CROSS && MU == 3) lds_put<R, 9>(lds.X, lane, X);
     __syncthreads();
     M3<R> A;
-    if constexpr (kTermsApart<R, TWOB>) {
-        // each term weighted and added in turn
-        const R wu = s.layer ? w1 : w0;
-        auto lower = [&](Step d) { return (s.layer ^ d.flip) ? w1 : w0; };
-        set_zero(A);
-        scale_acc(A, lds_get<R, 9>(lds.D[0], lane), wu);
-        scale_acc(A, lds_get<R, 9>(lds.D[0] + 9, lane), lower(step_of<kNu0<MU>, -1>(g, s)));
+    if constexpr (TWOB) {
+        A = lds_get<R, 9>(lds.D[0], lane);
         scale_acc(A, lds_get<R, 9>(lds.D[1], lane), wu);
-        scale_acc(A, lds_get<R, 9>(lds.D[1] + 9, lane), lower(step_of<kNu1<MU>, -1>(g, s)));
+        scale_acc(A, lds_get<R, 9>(lds.dn, lane), (s.layer ^ step_of<kNu1<MU>, -1>(g, s).flip) ? w1 : w0);
         scale_acc(A, D, wu);
-        scale_acc(A, X, lower(dn));
+        scale_acc(A, X, wd);
     } else {
         A = lds_get<R, 9>(lds.D[0], lane);
         add_to(A, lds_get<R, 9>(lds.D[1], lane));
@@ -236,7 +247,7 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
 }
 
 template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG, bool SIX>
-__global__ __launch_bounds__(SIX ? 384 : 192, kSplitWaves<R>) void k_pass_split(
+__global__ __launch_bounds__(SIX ? 384 : 192, (kSplitWaves<R, TWOB>)) void k_pass_split(
     store_t<R> *__restrict__ links, const Geom g, const int par, const R q32, const R w0, const R w1,
     const uint64_t sweep, const uint64_t seed, const int nhit, unsigned long long *__restrict__ counters,
     double *__restrict__ meas)
