@@ -600,7 +600,7 @@ hipError_t launch_plaquette(int precision, const void *links, const Geom &g, dou
         k_plaq_final<<<1, kSumBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
         return hipGetLastError();
     }
-    const int nblk = plaq_blocks(g);
+    const int nblk = plaq_tile_blocks(g);
     const long long tiles = ((long long)g.Vh + 63) / 64;
     const int tpb = (int)((tiles + nblk - 1) / nblk);
     const double tol = unitarity_tol(precision);

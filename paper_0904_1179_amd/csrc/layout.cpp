@@ -163,7 +163,13 @@ int pass_blocks(const Geom &g, int nb) { return (int)ceil_div((long long)g.nlat 
 // with 4096 workgroups of up to two tiles).
 static int even_blocks(long long n, int most) { return (int)ceil_div(n, ceil_div(n, most)); }
 
-int plaq_blocks(const Geom &g) { return even_blocks(ceil_div(g.Vh, 64), kPlaqBlocksMax); }
+int plaq_tile_blocks(const Geom &g) { return even_blocks(ceil_div(g.Vh, 64), kPlaqBlocksMax); }
+
+int plaq_blocks(const Geom &g)
+{
+    const long long need = ceil_div(g.Vh, kBlock);
+    return (int)(need < kPlaqBlocksMax ? need : kPlaqBlocksMax);
+}
 
 // The plaquette walk (one thread per column and chunk of x3, which reads
 // each link as an own link and as a neighbour in the same step of the walk)
@@ -193,15 +199,11 @@ int meas_blocks(const Geom &g, int lanes) { return pass_blocks(g, pass_links_per
 int polyakov_blocks(const Geom &g) { return (int)ceil_div((long long)g.L[0] * g.L[1] * g.L[2], kBlock); }
 
 // Plaquette partials: per layer and workgroup the plaquette sum, then the
-// number of links that fail the unitarity check.  They begin at kOffPartials
-// and may run on into the measured-pass partials, 24 nlat bytes or more per 64
-// half-indices: either region is written and summed up within one call, in
-// stream order, and holds nothing between calls.
-size_t meas_offset(const Geom &g)
-{
-    const long long slots = ceil_div(g.Vh, kBlock);
-    return (size_t)round_up(kOffPartials + 2 * 8LL * g.nlat * (slots < kPlaqBlocksMax ? slots : kPlaqBlocksMax), 256);
-}
+// number of links that fail the unitarity check.  plaq_blocks(g) of them have
+// room of their own; the others (plaq_tile_blocks) run on into the measured-pass
+// partials, 24 nlat bytes or more per 64 half-indices: either set is written
+// and summed up within one call, in stream order, and holds nothing between calls.
+size_t meas_offset(const Geom &g) { return (size_t)round_up(kOffPartials + 2 * 8LL * g.nlat * plaq_blocks(g), 256); }
 
 // measured-pass partials: 3 passes x nlat doubles per workgroup
 size_t polyakov_offset(const Geom &g)

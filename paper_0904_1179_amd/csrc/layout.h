@@ -40,8 +40,10 @@ bool pass_six_waves(int precision, bool hit1, long long tiles);
 int pass_links_per_block(const Geom &g, int lanes);
 // workgroups covering the nlat * Vh links of one pass, nb links each
 int pass_blocks(const Geom &g, int nb);
-// plaquette reduction: workgroups per layer (the most any plaquette kernel uses)
+// plaquette partials per layer with room of their own
 int plaq_blocks(const Geom &g);
+// workgroups per layer of the plaquette by tiles (its partials: meas_offset)
+int plaq_tile_blocks(const Geom &g);
 // Chunks of x3 per column of the plaquette walk (k_plaq_walk) for links of
 // the given precision, or 0 where the per-site kernels run instead (FP32, and
 // lattices too small to walk).
