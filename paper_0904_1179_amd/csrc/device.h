@@ -267,29 +267,34 @@ __host__ __device__ inline float cospi_sq_0to2(float t)
     return ((int)q & 1) ? s * s : c * c;
 }
 
-// 1/sqrt(x) and sqrt(x) for x > 0 (normal numbers).  FP64: the hardware
-// estimate y (2^-23) with one third-order correction, y + y e (1/2 + 3 e/8),
-// e = 1 - x y^2, about an ulp (on 5e8 arguments the same as the library's
-// rsqrt, which also handles zeros and infinities); a correctly rounded square
-// root and division take three times the instructions.
+// 1/sqrt(x) for x >= 0 (0 gives inf, inf gives 0, NaN gives NaN) and sqrt(x) for
+// finite x > 0.  FP64: the hardware estimate y (2^-23) with one third-order
+// correction, y + y e (1/2 + 3 e/8), e = 1 - x y^2, about an ulp; a correctly
+// rounded square root and division take three times the instructions.  Where y
+// is inf or 0, x y^2 is NaN: e is then taken as 1, which leaves y as it is.
+__device__ __forceinline__ double rsqrt_corrected(double y, double e) { return fma(y * e, fma(e, 0.375, 0.5), y); }
 __device__ __forceinline__ double rsqrt_r(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * y), y, 1.0);
-    return fma(y * e, fma(e, 0.375, 0.5), y);
+    return rsqrt_corrected(y, fmin(fma(-(x * y), y, 1.0), 1.0));
 }
-__device__ __forceinline__ double sqrt_pos_r(double x) { return x * rsqrt_r(x); }
+__device__ __forceinline__ double sqrt_pos_r(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    return x * rsqrt_corrected(y, fma(-(x * y), y, 1.0));
+}
 // FP32: correctly rounded square root and reciprocal.  The reciprocal is the
 // general division's own refinement without its scaling, which only acts on
 // operands near the ends of the exponent range; s is the root of a float, so
-// it lies in [2^-75, 2^64].
+// it lies in [2^-75, 2^64] unless it is 0 or inf (the estimate's own result then).
 __device__ __forceinline__ float rsqrt_r(float x)
 {
     const float s = sqrtf(x);
-    float r = __builtin_amdgcn_rcpf(s);
-    r = fmaf(fmaf(-s, r, 1.0f), r, r);
-    float q = fmaf(fmaf(-s, r, 1.0f), r, r);
-    return fmaf(fmaf(-s, q, 1.0f), r, q);
+    const float r0 = __builtin_amdgcn_rcpf(s);
+    const float r = fmaf(fmaf(-s, r0, 1.0f), r0, r0);
+    const float q = fmaf(fmaf(-s, r, 1.0f), r, r);
+    constexpr int kZeroOrInf = 0x264;
+    return __builtin_amdgcn_classf(s, kZeroOrInf) ? r0 : fmaf(fmaf(-s, q, 1.0f), r, q);
 }
 __device__ __forceinline__ float sqrt_pos_r(float x) { return sqrtf(x); }
 

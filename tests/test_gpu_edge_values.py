@@ -1,0 +1,50 @@
+"""GPU tests of links and couplings at the ends of the floating-point range:
+rows whose squared norm is 0 or overflows, NaN rows, and couplings so large
+that projections of twice the size would overflow.  The library treats them as
+the plain arithmetic of the FP64 oracle does."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_0904_1179_amd as hb_
+
+    return hb_
+
+
+def _same(got, want, tol):
+    """Equal where not finite, within tol elsewhere."""
+    f = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), f)
+    assert np.array_equal(got[~f], want[~f], equal_nan=True)
+    assert np.abs(got[f] - want[f]).max() < tol
+
+
+def test_reunitarise_rows_of_any_norm(hb):
+    """A row whose squared norm overflows becomes 0, one whose squared norm is
+    0 becomes inf or NaN by the sign of each entry; other rows and links are
+    as usual.  Rows 0 and 1, which are stored."""
+    from oracle import su3ref
+
+    ref = su3ref.Oracle((4, 4, 4, 4), seed=8)
+    ref.start(True)
+    links = ref.links().copy()
+    for k, (lo, hi, f) in enumerate([(0, 6, 1e160), (6, 12, 1e160), (0, 6, 1e-200), (0, 6, 0.0), (6, 12, 0.0),
+                                     (0, 6, 1e-155), (0, 12, 1e-150), (0, 12, 1e150)]):
+        links[4 * k + 3, lo:hi] *= f
+    links[101, 0] = np.inf
+    links[105, 8] = np.nan
+    lat = hb.Lattice((4, 4, 4, 4), seed=8)
+    lat.set_links(links)
+    ref.set_links(links)
+    lat.reunitarise()
+    ref.reunitarise()
+    # 1e-155: the squared norm is subnormal, 1e-310 with 2^-1074 the last place, and so the norm off by up to 1e-14
+    _same(lat.get_links()[:, :12], ref.links()[:, :12], 1e-13)
