@@ -405,7 +405,8 @@ template <typename R> __device__ __forceinline__ int pool_slot(R u4sq, int sub, 
 // lane of LDS (several attempts).
 // All 64 lanes take part; only the `active` ones count.  There is no branch
 // per lane: a rejected attempt (3 % of them, so nearly every wave has one)
-// rotates by the identity, which leaves finite rows as they are.  Returns
+// rotates by the identity, which leaves finite rows as they are (and carries a
+// NaN of one row into others: keep_nan_rows).  Returns
 // Re Tr W after the last subgroup, i.e. Re Tr(U_new A) before the final
 // reunitarisation.  Projections are of 2 v; the factor is exact and cancels.
 template <typename R, bool HIT1, typename First, typename Second>
@@ -489,6 +490,32 @@ __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint
     reunit(Ud);
     U = convert<R>(Ud);
     return double(W.e[0][0].re) + double(W.e[1][1].re) + double(W.e[2][2].re);
+}
+
+// A link that was stored with a NaN in row 0 or 1 has two rows of W NaN and so
+// every projection: it accepts no attempt and keeps its rows, reunitarised.
+// The heat bath's identity rotations have made its row 0 NaN throughout.
+template <typename R> __device__ __forceinline__ bool has_nan(const M3<R> &m)
+{
+    bool r = false;
+#pragma unroll
+    for (int e = 0; e < kEntries; ++e) {
+        const Cx<R> c = m.e[e / 3][e % 3];
+        r = r || c.re != c.re || c.im != c.im;
+    }
+    return r;
+}
+template <typename R, typename O> __device__ __forceinline__ void keep_nan_rows(M3<R> &U, Block<R> own, O o)
+{
+    if (__ballot(U.e[0][0].re != U.e[0][0].re) == 0) return;
+    M3<R> V;
+    load_own(V, own, o);
+    if (has_nan(V)) {
+        rebuild_row2(V);
+        M3<double> Vd = convert<double>(V);
+        reunit(Vd);
+        U = convert<R>(Vd);
+    }
 }
 
 // Re Tr(u s), accumulated in FP64.

@@ -216,6 +216,7 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
                 return draw_get<R>(lds.pool, made ? slot : 0);
             }
         });
+    keep_nan_rows(U, own, at.here);
     if (active) store_own(own, at.here, U);
     add_counts(n, counters, slot, lane);
     if constexpr (MEAS) {

@@ -48,3 +48,32 @@ def test_reunitarise_rows_of_any_norm(hb):
     ref.reunitarise()
     # 1e-155: the squared norm is subnormal, 1e-310 with 2^-1074 the last place, and so the norm off by up to 1e-14
     _same(lat.get_links()[:, :12], ref.links()[:, :12], 1e-13)
+
+
+@pytest.mark.parametrize("nlat,nhit", [(1, 1), (1, 3), (2, 1)])
+@pytest.mark.parametrize("precision", [64, 32])
+def test_a_nan_row_stays_in_its_row(hb, nlat, nhit, precision):
+    """A link with a NaN in its row 1 gets no update: its projections are NaN,
+    every attempt is rejected, and row 0 stays as it was; its neighbours'
+    staples are NaN, and they stay too.  Links and counters as the oracle's,
+    FP32 links within the rounding of a sweep where they hold no update."""
+    from oracle import su3ref
+
+    L = (4, 4, 4, 6)
+    ref = su3ref.Oracle(L, nlat=nlat, flip_mask=7 if nlat == 2 else None, nhit=nhit, seed=5)
+    ref.start(True)
+    links = ref.links().copy()
+    links[17, 6:18] = np.nan  # row 2 is rebuilt from rows 0 and 1
+    lat = hb.Lattice(L, nlat=nlat, precision=precision, nhit=nhit, seed=5)
+    lat.set_links(links)
+    ref.set_links(links)
+    lat.sweep(1, 5.7)
+    ref.sweep(1, 5.7)
+    got, want = lat.get_links()[:, :12], ref.links()[:, :12]
+    assert np.isfinite(want[17, :6]).all() and np.isnan(want[17, 6:]).all()
+    if precision == 64:
+        _same(got, want, 1e-12)
+        assert lat.counters()[1:] == ref.counters()
+    else:
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.abs(got[17, :6] - want[17, :6]).max() < 1e-6
