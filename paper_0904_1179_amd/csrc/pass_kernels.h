@@ -145,7 +145,7 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
             }
         }
     });
-    // A += the two terms of a direction, each with the coupling of its base's layer
+    // A += the two terms of a direction, each with half the coupling of its base's layer
     const R wu = s.layer ? w1 : w0, wd = (s.layer ^ dn.flip) ? w1 : w0;
     if (w != 0) {
         if constexpr (TWOB) {
@@ -302,7 +302,9 @@ template <typename R> R q32_of(double beta) { return R(1.5) / R(beta); }
 template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG> void launch_one(const PassArgs &a)
 {
     const unsigned grid = (unsigned)pass_blocks(a.g, kPassBlock);
-    const R q = TWOB ? R(1.5) : q32_of<R>(a.beta0), w0 = R(a.beta0), w1 = R(a.beta1);
+    // per-layer couplings: half of each goes into the staple, whose projections
+    // (of 2 v) then overflow no sooner than those of the full weights would
+    const R q = TWOB ? R(0.75) : q32_of<R>(a.beta0), w0 = R(0.5) * R(a.beta0), w1 = R(0.5) * R(a.beta1);
     if constexpr (!BIG)
         if (a.six_waves) {
             k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, true><<<grid, 384, 0, a.stream>>>(

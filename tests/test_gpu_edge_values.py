@@ -77,3 +77,22 @@ def test_a_nan_row_stays_in_its_row(hb, nlat, nhit, precision):
     else:
         assert np.array_equal(np.isnan(got), np.isnan(want))
         assert np.abs(got[17, :6] - want[17, :6]).max() < 1e-6
+
+
+@pytest.mark.parametrize("precision,beta", [(64, 1.5e153), (32, 2e18)])
+@pytest.mark.parametrize("nhit", [1, 2])
+def test_layer_couplings_near_the_overflow(hb, precision, beta, nhit):
+    """A cold double-layered torus: every staple is 6 beta, whose square is
+    finite; that of 12 beta is not.  Every attempt is accepted, as the oracle's."""
+    from oracle import su3ref
+
+    L = (4, 4, 4, 4)
+    lat = hb.Lattice(L, nlat=2, precision=precision, nhit=nhit, seed=8)
+    ref = su3ref.Oracle(L, nlat=2, flip_mask=7, nhit=nhit, seed=8)
+    lat.start(False)
+    ref.start(False)
+    lat.sweep_betas(1, beta, beta)
+    ref.sweep_betas(1, beta, beta)
+    assert lat.counters()[1:] == ref.counters()
+    assert ref.counters()[0] == ref.counters()[1]
+    _same(lat.get_links(), ref.links(), 1e-12 if precision == 64 else 1e-6)
