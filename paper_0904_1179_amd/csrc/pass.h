@@ -1,6 +1,6 @@
 // pass.h -- device code of one heat-bath pass: addressing, staples, random
 // draws and the Cabibbo-Marinari heat bath.  Shared by the single-lattice and
-// the batched kernels of pass.hip.
+// the batched kernels of pass_kernels.h.
 //
 // What bounds a pass.  A SIMD issues one vector instruction per 4 cycles, FP64,
 // FP32 and 64-bit integer alike (moves and bit operations in half of that when
@@ -357,24 +357,26 @@ template <typename R, int N> __device__ __forceinline__ M3<R> lds_get(const stor
     return m;
 }
 
-// A draw in LDS, slot-major over the 64 lanes.
-template <typename R> __device__ __forceinline__ void draw_put(store_t<R> (*buf)[64], int lane, const KPDraw<R> &d)
+// The draws of 64 lanes in LDS.
+template <typename R> struct DrawLds {
+    store_t<R> q_u4sq[64], cth_sc[64];
+    R ss[64];
+};
+template <typename R> __device__ __forceinline__ void draw_put(DrawLds<R> &buf, int lane, const KPDraw<R> &d)
 {
-    store_t<R> a, b, c;
+    store_t<R> a, b;
     a.x = d.q;
     a.y = d.u4sq;
     b.x = d.cth;
     b.y = d.sc;
-    c.x = d.ss;
-    c.y = R(0);
-    buf[0][lane] = a;
-    buf[1][lane] = b;
-    buf[2][lane] = c;
+    buf.q_u4sq[lane] = a;
+    buf.cth_sc[lane] = b;
+    buf.ss[lane] = d.ss;
 }
-template <typename R> __device__ __forceinline__ KPDraw<R> draw_get(const store_t<R> (*buf)[64], int lane)
+template <typename R> __device__ __forceinline__ KPDraw<R> draw_get(const DrawLds<R> &buf, int lane)
 {
-    const store_t<R> a = buf[0][lane], b = buf[1][lane];
-    return KPDraw<R>{a.x, a.y, b.x, b.y, buf[2][lane].x};
+    const store_t<R> a = buf.q_u4sq[lane], b = buf.cth_sc[lane];
+    return KPDraw<R>{a.x, a.y, b.x, b.y, buf.ss[lane]};
 }
 
 // Attempts and acceptances of a wave, uniform over it.
@@ -399,22 +401,39 @@ template <typename R> __device__ __forceinline__ int pool_slot(R u4sq, int sub, 
     return may && rank < kPoolSlots ? sub * kPoolSlots + rank : -1;
 }
 
-// The heat bath proper.  first(sub): the draw of attempt 0, made ahead;
-// second(sub, u4sq, made): that of attempt 1 where made is set (several
-// attempts; u4sq: the first draw's).  q32 = 3/(2 beta).  park: 18 entries per
-// lane of LDS (several attempts).
+// Has the matrix formed here, not later.
+template <typename R> __device__ __forceinline__ void pin(M3<R> &m)
+{
+#pragma unroll
+    for (int e = 0; e < 9; ++e) __asm__ __volatile__("" : "+v"(m.e[e / 3][e % 3].re), "+v"(m.e[e / 3][e % 3].im));
+}
+
+// The heat bath proper.  Returns Re Tr W after the last subgroup, i.e.
+// Re Tr(U_new A) before the final reunitarisation.  Projections are of 2 v; the
+// factor is exact and cancels.  q32 = 3/(2 beta).
 // All 64 lanes take part; only the `active` ones count.  There is no branch
 // per lane: a rejected attempt (3 % of them, so nearly every wave has one)
 // rotates by the identity, which leaves finite rows as they are (and carries a
-// NaN of one row into others: keep_nan_rows).  Returns
-// Re Tr W after the last subgroup, i.e. Re Tr(U_new A) before the final
-// reunitarisation.  Projections are of 2 v; the factor is exact and cancels.
-template <typename R, bool HIT1, typename First, typename Second>
+// NaN of one row into others: keep_nan_rows).
+//
+// The draw of attempt 0 is made ahead, first(sub), and that of attempt 1 for
+// some lanes, second(sub, u4sq, made), u4sq being the first draw's: PARK, the
+// wave then has registers for U and W but not for a draw beside them, and
+// leaves them in park_u and park_w (nine entries per lane of LDS each) during
+// any further one.  Without PARK all attempts of several are made here.
+// MASK: lanes that want no attempt are masked off.  Drawing in all of them
+// takes power and so clock rate (one wave per tile, 32^4 to 64^4 FP64: +3 to
+// +5 %; three waves, FP32 32^4 +3 %); waves that wait for the chain of
+// instructions and not for the clock lose up to 15 % by the branch.
+template <typename R, bool HIT1, bool PARK, bool MASK, typename First, typename Second>
 __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint32_t lid, uint64_t sweep, uint64_t seed,
-                                           int nhit, bool active, Counts &n, store_t<R> (*park)[64], int lane,
-                                           First first, Second second)
+                                           int nhit, bool active, Counts &n, store_t<R> (*park_u)[64],
+                                           store_t<R> (*park_w)[64], int lane, First first, Second second)
 {
     M3<R> W = mul_nn(U, A);
+    // without this, rows that the first subgroup does not read are formed after its round of attempts,
+    // and everything they are made of waits in registers
+    if constexpr (!HIT1) pin(W);
 #pragma unroll
     for (int sub = 0; sub < 3; ++sub) {
         const int i = (sub == 1) ? 1 : 0;
@@ -428,40 +447,67 @@ __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint
         const bool sample = k2 != R(0);
         const R rk = rsqrt_r(k2);
         const R inv2alpha = q32 * rk;
-        KPDraw<R> d = first(sub);
-        R lam2 = -d.q * inv2alpha;
-        bool ok = sample && d.u4sq <= R(1) - lam2;
-        n.att += lanes_of(sample && active);
-        n.acc += lanes_of(ok && active);
+        KPDraw<R> d;
+        R lam2;
+        bool ok;
+        // the lanes whose turn it is take this draw's values if it hits
+        const auto take = [&](const KPDraw<R> &e, bool turn) {
+            const R l = -e.q * inv2alpha;
+            const bool hit = turn && e.u4sq <= R(1) - l;
+            lam2 = hit ? l : lam2;
+            d.cth = hit ? e.cth : d.cth;
+            d.sc = hit ? e.sc : d.sc;
+            d.ss = hit ? e.ss : d.ss;
+            ok = ok || hit;
+        };
+        int t = 1;  // attempts that all lanes have had which still want one
+        if constexpr (HIT1 || PARK) {
+            d = first(sub);
+            lam2 = -d.q * inv2alpha;
+            ok = sample && d.u4sq <= R(1) - lam2;
+            n.att += lanes_of(sample && active);
+            n.acc += lanes_of(ok && active);
+        } else {
+            d = KPDraw<R>{};
+            lam2 = R(0);
+            ok = false;
+            t = 0;
+        }
         if constexpr (!HIT1) {
-            // a lane that has missed takes the next draw's values if that one hits
-            auto again = [&](const KPDraw<R> &e, bool turn) {
-                const R l = -e.q * inv2alpha;
-                const bool hit = turn && e.u4sq <= R(1) - l;
-                n.att += lanes_of(turn && active);
-                n.acc += lanes_of(hit && active);
-                lam2 = hit ? l : lam2;
-                d.cth = hit ? e.cth : d.cth;
-                d.sc = hit ? e.sc : d.sc;
-                d.ss = hit ? e.ss : d.ss;
-                ok = ok || hit;
-            };
             bool made = false;
-            if (nhit > 1) {
-                const KPDraw<R> e = second(sub, d.u4sq, made);
-                again(e, sample && !ok && made);
+            if constexpr (PARK) {
+                if (nhit > 1) {
+                    const KPDraw<R> e = second(sub, d.u4sq, made);
+                    const bool turn = sample && !ok && made && active;
+                    take(e, turn);
+                    n.att += lanes_of(turn);
+                    n.acc += lanes_of(turn && ok);
+                    if (__ballot(active && sample && !ok && !made) == 0) t = 2;
+                }
             }
-            // rare: U and W wait in LDS, so that the draw has the registers
-            for (int t = __ballot(sample && !ok && !made) != 0 ? 1 : 2; t < nhit && __ballot(sample && !ok) != 0; ++t) {
-                const bool turn = sample && !ok && (t > 1 || !made);
-                lds_put<R, 9>(park, lane, U);
-                lds_put<R, 9>(park + 9, lane, W);
-                __asm__ __volatile__("" ::: "memory");
-                const KPDraw<R> e = kp_draw<R>(lid, sweep, seed, sub, t);
-                __asm__ __volatile__("" ::: "memory");
-                U = lds_get<R, 9>(park, lane);
-                W = lds_get<R, 9>(park + 9, lane);
-                again(e, turn);
+            // Each lane its own attempt; without PARK as long as most lanes want one, there is one left or none
+            // has had three.
+            uint64_t m = __ballot(active && sample && !ok);
+            while (t < nhit && m != 0 && (PARK || t < 3 || t + 1 == nhit || __popcll(m) > 32)) {
+                const bool turn = active && sample && !ok && (t > 1 || !made);
+                if constexpr (PARK) {
+                    lds_put<R, 9>(park_u, lane, U);
+                    lds_put<R, 9>(park_w, lane, W);
+                    __asm__ __volatile__("" ::: "memory");
+                }
+                if constexpr (!MASK)
+                    take(kp_draw<R>(lid, sweep, seed, sub, t), turn);
+                else if (turn)
+                    take(kp_draw<R>(lid, sweep, seed, sub, t), true);
+                if constexpr (PARK) {
+                    __asm__ __volatile__("" ::: "memory");
+                    U = lds_get<R, 9>(park_u, lane);
+                    W = lds_get<R, 9>(park_w, lane);
+                }
+                n.att += lanes_of(turn);
+                n.acc += lanes_of(turn && ok);
+                ++t;
+                m = __ballot(active && sample && !ok);
             }
         }
         const R a0 = R(1) - R(2) * lam2;
@@ -549,6 +595,22 @@ __device__ __forceinline__ void add_counts(Counts n, unsigned long long *__restr
     }
 }
 
+// The job of tile t: the last one whose tile_begin is at most t.  The lanes of
+// a wave look at 64 jobs at once.
+__device__ __forceinline__ int job_of_tile(const BatchJob *__restrict__ jobs, int njobs, int t)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = njobs;
+    while (n > 1) {
+        const int stride = (n + 63) / 64, k = lane * stride;
+        const int c = (int)lanes_of(k < n && jobs[lo + (k < n ? k : 0)].tile_begin <= t);  // job lo always counts
+        lo += (c - 1) * stride;
+        n = min(stride, n - (c - 1) * stride);
+        if (stride == 1) break;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
 // Tile of this workgroup in a pass of parity `par`.  Every pass reads the
 // whole lattice, and the passes of a sweep alternate in parity, so the odd
 // passes walk the tiles backwards: a pass begins on the links its
@@ -558,6 +620,17 @@ __device__ __forceinline__ int pass_tile(int par)
 {
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     return par ? (int)gridDim.x - 1 - t : t;
+}
+
+// The couplings as the kernels take them: 3/(2 beta), or, for per-layer
+// couplings, half of each, which goes into the staple.  Its projections (of 2 v)
+// then overflow no sooner than those of the full weights would.
+template <typename R> struct Couplings {
+    R q32, w0, w1;
+};
+template <typename R, bool TWOB> Couplings<R> couplings_of(const PassArgs &a)
+{
+    return Couplings<R>{TWOB ? R(0.75) : R(1.5) / R(a.beta0), R(0.5) * R(a.beta0), R(0.5) * R(a.beta1)};
 }
 
 }  // namespace

@@ -10,20 +10,22 @@
 namespace su3hb {
 namespace {
 
-// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed
-// and 152 taken.  Asked for four waves, the compiler schedules for registers
-// and the pass is 10 % slower; held to exactly three it is 3 % slower.  FP32
-// with per-layer couplings has two more terms in registers and spills at five.
+// Waves per SIMD the kernels are compiled for.  FP64: 168 registers are allowed;
+// 1-hit passes take 152 to 168 (a measured one of two layers spills 8 to 24
+// bytes), several attempts 157 (measured ones and those with layer couplings
+// spill 60 to 72 bytes).  Asked for four waves, the compiler schedules for
+// registers and the pass is 10 % slower; held to exactly three it is 3 % slower.
+// FP32 with per-layer couplings has two more terms in registers and spills at five.
 template <typename R, bool TWOB = false> constexpr int kSplitWaves = sizeof(R) == 8 ? 3 : TWOB ? 4 : 5;
 
 // Several attempts: the second draws.  Six waves make them for every link and
 // subgroup; three for the lanes that pool_slot picks, whose links are listed.
 template <typename R, bool HIT1, bool SIX> struct SecondDraws {};
 template <typename R> struct SecondDraws<R, false, true> {
-    store_t<R> second[3][3][64];
+    DrawLds<R> second[3];
 };
 template <typename R> struct SecondDraws<R, false, false> {
-    store_t<R> pool[3][64];
+    DrawLds<R> pool;
     uint32_t list[64];
 };
 
@@ -34,27 +36,49 @@ template <typename R> struct LowerTerm<R, true> {
     store_t<R> dn[9][64];
 };
 
-template <typename R, bool HIT1, bool TWOB, bool KEEP, bool SIX>
-struct SplitLds : SecondDraws<R, HIT1, SIX>, LowerTerm<R, TWOB> {
+// Several attempts: U and W wait in LDS during a round of further ones, over the
+// two D, which wave 0 alone reads and has read by then.  A measured pass of mu = 1
+// or 2 needs D of the directions below mu again (KEEP; their sum stays in D[0])
+// and has a place of its own for W.
+template <typename R, bool OWN> struct Parking {};
+template <typename R> struct Parking<R, true> {
+    store_t<R> w[9][64];
+};
+template <typename R, bool HIT1, bool TWOB, bool KEEP, bool SIX, bool ROOM = TWOB>
+struct SplitLds : SecondDraws<R, HIT1, SIX>, LowerTerm<R, TWOB>, Parking<R, !HIT1 && KEEP> {
     store_t<R> D[2][9][64];  // D of the first two directions
-    store_t<R> draw[SIX ? 3 : 2][3][64];
-    // where U and W wait for a further attempt: over D, unless a measurement reads it later
-    __device__ store_t<R> (*parking())[64] { return D[0]; }
+    // wave 0 keeps its own draw in registers, unless these are short
+    static constexpr bool kAllDraws = SIX || (!HIT1 && ROOM);
+    DrawLds<R> draw[kAllDraws ? 3 : 2];
+    __device__ store_t<R> (*park_u())[64] { return D[1]; }
+    __device__ store_t<R> (*park_w())[64]
+    {
+        if constexpr (!HIT1 && KEEP)
+            return this->w;
+        else
+            return D[0];
+    }
 };
-template <typename R, bool TWOB, bool SIX> struct SplitLds<R, false, TWOB, true, SIX> : SecondDraws<R, false, SIX> {
-    store_t<R> D[2][9][64];
-    store_t<R> draw[SIX ? 3 : 2][3][64];
-    store_t<R> park[18][64];
-    __device__ store_t<R> (*parking())[64] { return park; }
+// A measured pass of a double-layered torus: the new link, after the heat bath
+// (several attempts: over D[1], which is free then).
+template <typename R, bool OWN> struct NewLink {};
+template <typename R> struct NewLink<R, true> {
+    store_t<R> U[9][64];
 };
-// A measured pass of a double-layered torus.
-template <typename R, bool HIT1, int MU, bool SIX> struct CrossLds : SplitLds<R, HIT1, false, true, SIX> {
-    store_t<R> U[9][64];                // the new link
+template <typename R, bool HIT1, int MU, bool SIX>
+struct CrossLds : SplitLds<R, HIT1, false, (MU < 3), SIX, true>, NewLink<R, HIT1> {
     store_t<R> X[MU == 3 ? 9 : 1][64];  // wave 0's cross-layer part
     double part[3][2];
+    __device__ store_t<R> (*new_link())[64]
+    {
+        if constexpr (HIT1)
+            return this->U;
+        else
+            return this->D[1];
+    }
 };
 template <typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, int MU, bool SIX>
-using PassLds = std::conditional_t<MEAS && DLT, CrossLds<R, HIT1, MU, SIX>, SplitLds<R, HIT1, TWOB, MEAS, SIX>>;
+using PassLds = std::conditional_t<MEAS && DLT, CrossLds<R, HIT1, MU, SIX>, SplitLds<R, HIT1, TWOB, MEAS && (MU < 3), SIX, TWOB || MEAS>>;
 
 // A wave's share of a measured tile per layer: tr is filed under the link's
 // layer but for its part trx, which belongs to the other one.
@@ -174,7 +198,7 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
         if constexpr (CROSS) {
             __syncthreads();
             double trx = 0.0;
-            if (nu < MU) trx = retr_mul(lds_get<R, 9>(lds.U, lane), X);
+            if (nu < MU) trx = retr_mul(lds_get<R, 9>(lds.new_link(), lane), X);
             cross_share(lds, active, s.layer != 0, 0.0, trx, w, lane);
             __syncthreads();
         }
@@ -184,24 +208,32 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
     M3<R> U;
     load_own(U, own, at.here);
     if constexpr (CROSS && MU == 3) lds_put<R, 9>(lds.X, lane, X);
+    if constexpr (!SIX && std::remove_reference_t<decltype(lds)>::kAllDraws) draw_put<R>(lds.draw[2], lane, mine);
     __syncthreads();
     M3<R> A;
     if constexpr (TWOB) {
-        A = lds_get<R, 9>(lds.D[0], lane);
-        scale_acc(A, lds_get<R, 9>(lds.D[1], lane), wu);
-        scale_acc(A, lds_get<R, 9>(lds.dn, lane), (s.layer ^ step_of<kNu1<MU>, -1>(g, s).flip) ? w1 : w0);
-        scale_acc(A, D, wu);
-        scale_acc(A, X, wd);
+        // entry by entry, so that D and X give way to A
+        const R wd1 = (s.layer ^ step_of<kNu1<MU>, -1>(g, s).flip) ? w1 : w0;
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+            const store_t<R> a = lds.D[0][e][lane], u1 = lds.D[1][e][lane], d1 = lds.dn[e][lane];
+            Cx<R> t{a.x, a.y};
+            t = scale_add(t, Cx<R>{u1.x, u1.y}, wu);
+            t = scale_add(t, Cx<R>{d1.x, d1.y}, wd1);
+            t = scale_add(t, D.e[e / 3][e % 3], wu);
+            A.e[e / 3][e % 3] = scale_add(t, X.e[e / 3][e % 3], wd);
+        }
     } else {
         A = lds_get<R, 9>(lds.D[0], lane);
         add_to(A, lds_get<R, 9>(lds.D[1], lane));
+        if constexpr (MEAS && MU == 2) lds_put<R, 9>(lds.D[0], lane, A);  // the sum over nu < MU
         add_to(A, D);
     }
     rebuild_row2(U);
     Counts n{0, 0};
-    double tr = heatbath<R, HIT1>(
-        U, A, q32, lid, sweep, seed, nhit, active, n, lds.parking(), lane,
-        [&](int k) { return !SIX && k == 2 ? mine : draw_get<R>(lds.draw[k], lane); },
+    double tr = heatbath<R, HIT1, !HIT1, !SIX && sizeof(R) == 4>(
+        U, A, q32, lid, sweep, seed, nhit, active, n, lds.park_u(), lds.park_w(), lane,
+        [&](int k) { return !std::remove_reference_t<decltype(lds)>::kAllDraws && k == 2 ? mine : draw_get<R>(lds.draw[k], lane); },
         [&](int k, R u4sq, bool &made) {
             if constexpr (HIT1) {
                 made = false;
@@ -221,19 +253,14 @@ __device__ __forceinline__ void pass_split(store_t<R> *__restrict__ links, const
     add_counts(n, counters, slot, lane);
     if constexpr (MEAS) {
         // S = sum of D_nu over nu < MU
-        if constexpr (MU == 1) tr = retr_mul(U, lds_get<R, 9>(lds.D[0], lane));
-        if constexpr (MU == 2) {
-            M3<R> S = lds_get<R, 9>(lds.D[0], lane);
-            add_to(S, lds_get<R, 9>(lds.D[1], lane));
-            tr = retr_mul(U, S);
-        }
+        if constexpr (MU < 3) tr = retr_mul(U, lds_get<R, 9>(lds.D[0], lane));
         if constexpr (!CROSS) {
             tr = wave_sum(active ? tr : 0.0);
             if (lane == 0) meas[0] = tr;
         } else {
             // the lower terms whose base lies in the other layer: each wave
             // sums its own direction's share Re Tr(U_new X)
-            lds_put<R, 9>(lds.U, lane, U);
+            lds_put<R, 9>(lds.new_link(), lane, U);
             __syncthreads();
             double trx = 0.0;
             if constexpr (MU == 3) trx = retr_mul(U, lds_get<R, 9>(lds.X, lane));
@@ -253,26 +280,12 @@ __global__ __launch_bounds__(SIX ? 384 : 192, (kSplitWaves<R, TWOB>)) void k_pas
     const uint64_t sweep, const uint64_t seed, const int nhit, unsigned long long *__restrict__ counters,
     double *__restrict__ meas)
 {
+    // three waves, several attempts: four workgroups share the 160 KiB of a CU, as many as the registers allow
+    static_assert(sizeof(PassLds<R, HIT1, DLT, MEAS, TWOB, MU, SIX>) <= (SIX || HIT1 ? 160 : 40) * 1024, "LDS of a pass");
     __shared__ PassLds<R, HIT1, DLT, MEAS, TWOB, MU, SIX> lds;
     pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, SIX>(links, g, par, pass_tile(par), q32, w0, w1, sweep, seed, nhit,
                                                   counters, blockIdx.x % kCounterSlots,
                                                   MEAS ? meas + (size_t)g.nlat * blockIdx.x : nullptr, lds);
-}
-
-// The job of tile t: the last one whose tile_begin is at most t.  The lanes of
-// a wave look at 64 jobs at once.
-__device__ __forceinline__ int job_of_tile(const BatchJob *__restrict__ jobs, int njobs, int t)
-{
-    const int lane = threadIdx.x & 63;
-    int lo = 0, n = njobs;
-    while (n > 1) {
-        const int stride = (n + 63) / 64, k = lane * stride;
-        const int c = (int)lanes_of(k < n && jobs[lo + (k < n ? k : 0)].tile_begin <= t);  // job lo always counts
-        lo += (c - 1) * stride;
-        n = min(stride, n - (c - 1) * stride);
-        if (stride == 1) break;
-    }
-    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // Batched pass: one launch updates the links U_MU of parity `par` of every
@@ -297,14 +310,10 @@ __global__ __launch_bounds__(SIX ? 384 : 192, kSplitWaves<R>) void k_batch_split
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
-template <typename R> R q32_of(double beta) { return R(1.5) / R(beta); }
-
 template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BIG> void launch_one(const PassArgs &a)
 {
     const unsigned grid = (unsigned)pass_blocks(a.g, kPassBlock);
-    // per-layer couplings: half of each goes into the staple, whose projections
-    // (of 2 v) then overflow no sooner than those of the full weights would
-    const R q = TWOB ? R(0.75) : q32_of<R>(a.beta0), w0 = R(0.5) * R(a.beta0), w1 = R(0.5) * R(a.beta1);
+    const auto [q, w0, w1] = couplings_of<R, TWOB>(a);
     if constexpr (!BIG)
         if (a.six_waves) {
             k_pass_split<MU, R, HIT1, DLT, MEAS, TWOB, BIG, true><<<grid, 384, 0, a.stream>>>(
