@@ -13,7 +13,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsu3hb.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("pass_f64.hip", "pass_f32.hip", "kernels.hip", "api.hip", "server.hip", "layout.cpp")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("pass_f64.hip", "pass_f32.hip", "pass_lane_f64.hip", "pass_lane_f32.hip",
+                                                   "kernels.hip", "api.hip", "server.hip", "layout.cpp")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=on: multiply-adds are fused only within one source expression,

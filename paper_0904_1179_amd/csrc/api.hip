@@ -168,7 +168,9 @@ su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nul
     a.beta1 = betas ? betas[1] : beta;
     a.twob = betas != nullptr;
     a.big = pass_big(c->g, c->p.precision);
-    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, pass_blocks(c->g, kPassBlock));
+    const long long tiles = pass_blocks(c->g, kPassBlock);
+    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, tiles);
+    a.one_lane = pass_one_lane(c->p.precision, c->p.nhit, std::min(a.beta0, a.beta1), meas != nullptr, a.twob, tiles);
     a.seed = c->p.seed;
     a.nhit = c->p.nhit;
     a.counters = counters_of(c);

@@ -32,6 +32,7 @@ struct PassArgs {
     bool twob;                     // double-layered torus: a plaquette takes its base site's layer coupling
     bool big;                      // 64-bit link offsets (pass_big)
     bool six_waves;                // six waves per 64 links instead of three (pass_six_waves)
+    bool one_lane;                 // one wave per 64 links, several attempts only (pass_one_lane)
     uint64_t sweep, seed;
     int nhit;
     unsigned long long *counters;
@@ -47,8 +48,11 @@ struct PassArgs {
 };
 hipError_t launch_pass_f64(const PassArgs &a);
 hipError_t launch_pass_f32(const PassArgs &a);
+hipError_t launch_lane_f64(const PassArgs &a);
+hipError_t launch_lane_f32(const PassArgs &a);
 inline hipError_t launch_pass(int precision, const PassArgs &a)
 {
+    if (a.one_lane) return precision == 64 ? launch_lane_f64(a) : launch_lane_f32(a);
     return precision == 64 ? launch_pass_f64(a) : launch_pass_f32(a);
 }
 
@@ -62,14 +66,17 @@ struct BatchArgs {
     int njobs, ntiles;
     long long step;
     int mu, par;
-    bool hit1, dlt, big, six_waves;
+    bool hit1, dlt, big, six_waves, one_lane;
     hipStream_t stream;
 };
 hipError_t launch_batch_f64(const BatchArgs &b);
 hipError_t launch_batch_f32(const BatchArgs &b);
+hipError_t launch_lane_batch_f64(const BatchArgs &b);
+hipError_t launch_lane_batch_f32(const BatchArgs &b);
 inline hipError_t launch_batch(int precision, const BatchArgs &b)
 {
     if (b.njobs <= 0 || b.ntiles <= 0) return hipSuccess;
+    if (b.one_lane) return precision == 64 ? launch_lane_batch_f64(b) : launch_lane_batch_f32(b);
     return precision == 64 ? launch_batch_f64(b) : launch_batch_f32(b);
 }
 

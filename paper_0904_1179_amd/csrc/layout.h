@@ -36,6 +36,9 @@ bool pass_big(const Geom &g, int precision);
 // Whether a pass of that many tiles of 64 links gives the random draws to three
 // waves of their own.
 bool pass_six_waves(int precision, bool hit1, long long tiles);
+// Whether a pass with several attempts runs one wave per tile; beta: the
+// smaller coupling of the layers, twob: each has its own.
+bool pass_one_lane(int precision, int nhit, double beta, bool measured, bool twob, long long tiles);
 // Links per workgroup of a pass (64, whatever the lanes).
 int pass_links_per_block(const Geom &g, int lanes);
 // workgroups covering the nlat * Vh links of one pass, nb links each

@@ -287,6 +287,30 @@ __device__ __forceinline__ void staple_nu(M3<R> &D, M3<R> &cross, const store_t<
     }
 }
 
+// The same from b and e (rows 0 and 1) at hand, in a wave that forms all three
+// directions in turn.
+template <int MU, typename R, bool CROSS, bool TWOB, bool BIG>
+__device__ __forceinline__ void staple_from(M3<R> &D, M3<R> &cross, M3<R> b, const M3<R> &e, const store_t<R> *links,
+                                            const Geom &g, int par, int nu, const StapleAt<BIG> &at)
+{
+    const Block<R> unu_par = block_of<R, BIG>(links, g, nu, par), unu_opp = block_of<R, BIG>(links, g, nu, par ^ 1);
+    M3<R> c, d, a, f;
+    load_rows_pair(c, unu_par, at.here, d, unu_par, at.mu_dn);
+    rebuild_row2(b);
+    rebuild_row2(d);
+    const M3<R> cb = mul_nn_su3(c, b);
+    const M3<R> ed = mul_nn_su3(e, d);
+    load_rows_pair(a, unu_opp, at.mu, f, unu_opp, at.dn);
+    D = mul_nd_su3(a, cb);
+    rebuild_row2(f);
+    if constexpr (TWOB) {
+        set_zero(cross);
+        acc_dn(cross, ed, f);
+    } else {
+        add_dn<R, CROSS>(D, ed, f, cross, at.crosses);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Cabibbo-Marinari heat bath of one link in staple A.  W = U A; for subgroup
 // (i,j): v = 1/2 (Re(w_ii + w_jj), -Im(w_ij + w_ji), Re(w_ji - w_ij),
@@ -401,6 +425,47 @@ template <typename R> __device__ __forceinline__ int pool_slot(R u4sq, int sub, 
     return may && rank < kPoolSlots ? sub * kPoolSlots + rank : -1;
 }
 
+// A round of 64 further attempts for the lanes of the mask m, each lane one: the
+// asking lanes get 64 / (their number) attempts each, which lanes rank, rank +
+// count, rank + 2 count, ... make.  So a wave at strong coupling, where all its
+// lanes may miss many times, waits for some tens of attempts, not for the
+// slowest lane's, and a single asker has all its attempts at once.
+struct Round {
+    int rank;        // of an asking lane among them
+    int asker;       // the lane whose attempt this one makes,
+    int ahead;       // and which of its `each` attempts
+    int each;
+    uint64_t every;  // bits 0, count, 2 count, ... below each count
+    uint32_t inv;
+    // x / count for x < 64, exact: inv = floor(2^16 / count) + 1 is above 2^16 / count by at most 1, and 64 < 2^16 / 64
+    __device__ __forceinline__ int attempts(int x) const { return (int)((uint32_t)x * inv >> 16); }
+    __device__ __forceinline__ Round(uint64_t m, int lane)
+    {
+        const int count = __popcll(m);
+        inv = 65536u / (uint32_t)count + 1;
+        each = 64 / count;
+        every = 1;
+        for (int s = count; s < each * count; s += s) every |= every << s;
+        if (each * count < 64) every &= (1ull << each * count) - 1;
+        const uint64_t below = (1ull << lane) - 1;
+        const bool asks = m >> lane & 1;
+        rank = __popcll(m & below);
+        // lane r learns which lane has rank r: the others take the ranks from count on
+        const int to = asks ? rank : count + __popcll(~m & below);
+        const int holder = __builtin_amdgcn_ds_permute(to << 2, lane);
+        ahead = attempts(lane);
+        asker = __shfl(holder, lane - ahead * count);
+    }
+};
+// Sum over the wave of a number below 128.
+__device__ __forceinline__ uint32_t sum_small(int x)
+{
+    uint32_t s = 0;
+#pragma unroll
+    for (int b = 0; b < 7; ++b) s += lanes_of(x >> b & 1) << b;
+    return s;
+}
+
 // Has the matrix formed here, not later.
 template <typename R> __device__ __forceinline__ void pin(M3<R> &m)
 {
@@ -509,6 +574,33 @@ __device__ __forceinline__ double heatbath(M3<R> &U, const M3<R> &A, R q32, uint
                 ++t;
                 m = __ballot(active && sample && !ok);
             }
+            // further attempts, a round of 64 at a time
+            if constexpr (!PARK)
+                while (t < nhit && m != 0) {
+                    const Round r(m, lane);
+                    const int at = t + r.ahead;
+                    const KPDraw<R> e = kp_draw<R>(__shfl(lid, r.asker), sweep, seed, sub, at);
+                    const R l = -e.q * __shfl(inv2alpha, r.asker);
+                    const bool hit = r.ahead < r.each && at < nhit && e.u4sq <= R(1) - l;
+                    // the asker takes the first of its attempts that hit, which lane `from` made
+                    const bool asks = m >> lane & 1;
+                    const uint64_t hits = __ballot(hit);
+                    const uint64_t mine = asks ? (hits >> r.rank) & r.every : 0;
+                    const bool got = mine != 0;
+                    const int skip = got ? __builtin_ctzll(mine) : 0;
+                    const int from = (r.rank + skip) & 63;
+                    const R lam = __shfl(l, from), cth = __shfl(e.cth, from), sc = __shfl(e.sc, from),
+                            ss = __shfl(e.ss, from);
+                    lam2 = got ? lam : lam2;
+                    d.cth = got ? cth : d.cth;
+                    d.sc = got ? sc : d.sc;
+                    d.ss = got ? ss : d.ss;
+                    ok = ok || got;
+                    n.att += sum_small(!asks ? 0 : got ? r.attempts(skip) + 1 : min(r.each, nhit - t));
+                    n.acc += lanes_of(got);
+                    t += r.each;
+                    m = __ballot(asks && !got);
+                }
         }
         const R a0 = R(1) - R(2) * lam2;
         const R rho2 = R(1) - a0 * a0;

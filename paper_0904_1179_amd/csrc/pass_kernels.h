@@ -108,11 +108,11 @@ __device__ __forceinline__ void cross_share(Lds &lds, bool active, bool l1, doub
 // lane per link (up to 8192 links four, up to 32768 two) -> this:
 //   FP64          8^4 9.6 -> 6.0, 16^4 12.9 -> 9.5, 2 x 16^4 18.1 -> 15.6, 24^4 35.6
 //                 -> 31.2, 32^4 98 -> 93, 64^4 1608 -> 1600;
-//   FP64, 3 hits  8^4 16.3 -> 9.2, 16^4 18.4 -> 14.1, 32^4 105 -> 103, 40^4 256 -> 260;
+//   FP64, 3 hits  8^4 16.3 -> 9.3, 16^4 18.4 -> 14.1, 32^4 106 -> 103 (larger ones: one wave, pass_lane.h);
 //   FP32          8^4 9.1 -> 5.7, 16^4 10.7 -> 7.4, 2 x 16^4 13.9 -> 10.2, 24^4 22.3 ->
 //                 19.4, 32^4 51.8 -> 48.5, 64^4 867 -> 856;
 //   FP32, 3 hits  16^4 19.2 -> 9.9, 32^4 65 -> 57, 64^4 1040 -> 974;
-//   measured, two layers, 2 x 16^4: FP64 19.2 -> 17.4, FP32 15.3 -> 11.6.
+//   measured sweeps (three of whose eight passes measure), 2 x 16^4: FP64 19.2 -> 17.4, FP32 15.3 -> 11.6.
 // What bounds it now: 32^4 FP64 moves 500 MB past L2 with the vector unit 57 %
 // busy (its loads and stores alone take 76 us, its arithmetic alone 64); FP32
 // keeps the vector unit 86 % busy; 8^4 has a quarter of a wave per SIMD and

@@ -47,7 +47,7 @@ struct Job {
 struct Group {
     BatchJob *d_table = nullptr;  // device copy
     int njobs = 0, ntiles = 0;
-    bool big = false;
+    bool big = false, one_lane = false;
 };
 
 }  // namespace
@@ -156,6 +156,12 @@ su3_status build_tables(su3_server *s)
         G.d_table = (BatchJob *)s->arena + (size_t)gi * s->max_active;
         G.njobs = (int)per[gi].size();
         G.ntiles = tiles;
+        // the kernel that suits most tiles of the batch
+        long long lane_tiles = 0;
+        for (const BatchJob &b : per[gi])
+            if (pass_one_lane(gi < 4 ? 64 : 32, b.nhit, 1.5 / b.q32, false, false, tiles))
+                lane_tiles += pass_blocks(b.g, kPassBlock);
+        G.one_lane = 2 * lane_tiles > tiles;
         if (G.njobs) {
             hipError_t e = hipMemcpyAsync(G.d_table, h, sizeof(BatchJob) * G.njobs, hipMemcpyHostToDevice, s->stream);
             if (e != hipSuccess) return hip_fail(e, "job table copy");
@@ -277,7 +283,7 @@ su3_status run_sweeps(su3_server *s, int32_t max_sweeps, int32_t *n_active, int3
                         if (!G.njobs) continue;
                         const BatchArgs b{G.d_table,     G.njobs,       G.ntiles, s->step, mu, par,
                                           (gi & 2) == 0, (gi & 1) != 0, G.big,
-                                          pass_six_waves(gi < 4 ? 64 : 32, (gi & 2) == 0, G.ntiles), s->stream};
+                                          pass_six_waves(gi < 4 ? 64 : 32, (gi & 2) == 0, G.ntiles), G.one_lane, s->stream};
                         e = launch_batch(gi < 4 ? 64 : 32, b);
                         if (e != hipSuccess) return hip_fail(e, "batched pass");
                     }
