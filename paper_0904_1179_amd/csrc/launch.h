@@ -32,7 +32,7 @@ struct PassArgs {
     bool twob;                     // double-layered torus: a plaquette takes its base site's layer coupling
     bool big;                      // 64-bit link offsets (pass_big)
     bool six_waves;                // six waves per 64 links instead of three (pass_six_waves)
-    bool one_lane;                 // one wave per 64 links, several attempts only (pass_one_lane)
+    bool one_lane;                 // one wave per 64 links, several attempts only (pass_one_lane); always with `big`
     uint64_t sweep, seed;
     int nhit;
     unsigned long long *counters;
@@ -52,7 +52,7 @@ hipError_t launch_lane_f64(const PassArgs &a);
 hipError_t launch_lane_f32(const PassArgs &a);
 inline hipError_t launch_pass(int precision, const PassArgs &a)
 {
-    if (a.one_lane) return precision == 64 ? launch_lane_f64(a) : launch_lane_f32(a);
+    if (a.one_lane || (a.big && a.nhit > 1)) return precision == 64 ? launch_lane_f64(a) : launch_lane_f32(a);
     return precision == 64 ? launch_pass_f64(a) : launch_pass_f32(a);
 }
 
@@ -76,7 +76,7 @@ hipError_t launch_lane_batch_f32(const BatchArgs &b);
 inline hipError_t launch_batch(int precision, const BatchArgs &b)
 {
     if (b.njobs <= 0 || b.ntiles <= 0) return hipSuccess;
-    if (b.one_lane) return precision == 64 ? launch_lane_batch_f64(b) : launch_lane_batch_f32(b);
+    if (b.one_lane || (b.big && !b.hit1)) return precision == 64 ? launch_lane_batch_f64(b) : launch_lane_batch_f32(b);
     return precision == 64 ? launch_batch_f64(b) : launch_batch_f32(b);
 }
 

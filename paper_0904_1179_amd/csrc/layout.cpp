@@ -159,7 +159,8 @@ bool pass_six_waves(int precision, bool hit1, long long tiles)
 // the others while these hold their registers or have ended.  So it takes
 // lattices where many attempts miss (beta below 4: those made ahead do not
 // cover them any more), unless few waves are there to share the work, and large
-// FP64 ones, whose waves wait for memory anyway.  us per pass, one wave / three
+// ones, whose waves wait for memory anyway (FP64 ones first; with layer couplings
+// the three waves spill).  us per pass, one wave / three
 // (six where these are in brackets), from one run each:
 //   FP64, 2 hits  16^4 beta 2 17.4 / 15.9, 24^4 beta 2 42.5 / 45.7, beta 3.5 42.5 / 42.3, beta 4.5
 //                 42.1 / 38.4, 32^4 beta 2 110 / 125, beta 4.5 108 / 107, 40^4 beta 4.5 257 / 263;
@@ -168,12 +169,13 @@ bool pass_six_waves(int precision, bool hit1, long long tiles)
 //   FP64, 64 hits 8^4 beta 0.5 41 [192], beta 2 24 [41];
 //   FP32, 2 hits  20^4 beta 2 19.4 / 17.0, 24^4 26.9 / 29.2, 32^4 60 / 67, beta 4.5 59.5 / 56.0;
 //   FP32, 8 hits  20^4 beta 2 28.0 / 35.9, beta 3.5 25.5 / 24.5;
+//   FP32, 3 hits, beta 5.7  40^4 141 / 139, 64^4 911 / 939, 48^4 measured 299 / 304;
 //   measured FP64, 2 hits  24^4 beta 5 43.8 / 40.4, 32^4 beta 5 110 / 113;
 //   layer couplings FP64, 2 hits, beta 5.7  2 x 12^4 16.8 / 13.7, 2 x 16^4 20.8 / 22.7, 2 x 32^4 213 / 279.
 bool pass_one_lane(int precision, int nhit, double beta, bool measured, bool twob, long long tiles)
 {
     if (nhit == 1) return false;
-    if (precision == 64 && tiles >= (twob ? 1024 : measured ? 8192 : 16384)) return true;
+    if (tiles >= (precision == 32 ? 32768 : twob ? 1024 : measured ? 8192 : 16384)) return true;
     if (beta >= 4.0) return false;
     if (tiles >= (precision == 64 ? 1024 : 2048)) return true;
     return nhit >= (pass_six_waves(precision, false, tiles) ? 16 : 6) && beta < (precision == 64 ? 4.0 : 3.0);

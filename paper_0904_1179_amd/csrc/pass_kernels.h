@@ -324,27 +324,23 @@ template <int MU, typename R, bool HIT1, bool DLT, bool MEAS, bool TWOB, bool BI
         (store_t<R> *)a.links, a.g, a.par, q, w0, w1, a.sweep, a.seed, a.nhit, a.counters, a.meas);
 }
 
+// The kernel by hit count and torus.  Blocks of 4 GiB and more (64-bit offsets)
+// have one attempt here: several take one wave per tile (launch_pass).
+template <int MU, typename R, bool MEAS, bool TWOB, bool DLT> void launch_torus(const PassArgs &a)
+{
+    if (a.big)
+        launch_one<MU, R, true, DLT, MEAS, TWOB, true>(a);
+    else if (a.nhit == 1)
+        launch_one<MU, R, true, DLT, MEAS, TWOB, false>(a);
+    else
+        launch_one<MU, R, false, DLT, MEAS, TWOB, false>(a);
+}
+
 template <int MU, typename R, bool MEAS, bool TWOB> void launch_mu(const PassArgs &a)
 {
-    // a lattice whose blocks reach 4 GiB: 64-bit offsets, in the variant that
-    // takes any hit count and any torus
-    if (a.big) return launch_one<MU, R, false, true, MEAS, TWOB, true>(a);
-    const bool hit1 = a.nhit == 1;
-    if constexpr (TWOB) {
-        if (hit1)
-            launch_one<MU, R, true, true, MEAS, TWOB, false>(a);
-        else
-            launch_one<MU, R, false, true, MEAS, TWOB, false>(a);
-    } else if (a.g.nlat == 2) {
-        if (hit1)
-            launch_one<MU, R, true, true, MEAS, TWOB, false>(a);
-        else
-            launch_one<MU, R, false, true, MEAS, TWOB, false>(a);
-    } else if (hit1) {
-        launch_one<MU, R, true, false, MEAS, TWOB, false>(a);
-    } else {
-        launch_one<MU, R, false, false, MEAS, TWOB, false>(a);
-    }
+    if constexpr (!TWOB)
+        if (a.g.nlat == 1) return launch_torus<MU, R, MEAS, TWOB, false>(a);
+    launch_torus<MU, R, MEAS, TWOB, true>(a);
 }
 
 template <typename R, bool MEAS, bool TWOB> void launch_any(const PassArgs &a)
@@ -380,18 +376,22 @@ template <int MU, typename R, bool HIT1, bool DLT, bool BIG> void launch_batch_o
     k_batch_split<MU, R, HIT1, DLT, BIG, false><<<b.ntiles, 192, 0, b.stream>>>(b.jobs, b.njobs, b.step, b.par);
 }
 
-template <int MU, typename R> void launch_batch_mu(const BatchArgs &b)
+template <int MU, typename R, bool DLT> void launch_batch_torus(const BatchArgs &b)
 {
     if (b.big)
-        launch_batch_one<MU, R, false, true, true>(b);
-    else if (b.dlt && b.hit1)
-        launch_batch_one<MU, R, true, true, false>(b);
-    else if (b.dlt)
-        launch_batch_one<MU, R, false, true, false>(b);
+        launch_batch_one<MU, R, true, DLT, true>(b);
     else if (b.hit1)
-        launch_batch_one<MU, R, true, false, false>(b);
+        launch_batch_one<MU, R, true, DLT, false>(b);
     else
-        launch_batch_one<MU, R, false, false, false>(b);
+        launch_batch_one<MU, R, false, DLT, false>(b);
+}
+
+template <int MU, typename R> void launch_batch_mu(const BatchArgs &b)
+{
+    if (b.dlt)
+        launch_batch_torus<MU, R, true>(b);
+    else
+        launch_batch_torus<MU, R, false>(b);
 }
 
 template <typename R> hipError_t launch_batch_r(const BatchArgs &b)

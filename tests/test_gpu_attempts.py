@@ -139,3 +139,43 @@ def test_equal_layer_couplings_as_one(hb, L, precision, nhit, beta):
         assert abs(a.counters()[1] - b.counters()[1]) <= 1e-4 * b.counters()[1]
     d = np.abs(a.get_links() - b.get_links()).max(axis=1)
     assert np.median(d) < (1e-13 if precision == 64 else 1e-5)
+
+
+@pytest.mark.parametrize("L,nlat,precision,kind", [
+    ((96, 96, 98, 100), 1, 64, "measure"),  # 45.2e6 links per block, 96 bytes each: just over 4 GiB
+    ((80, 80, 84, 84), 2, 64, "betas"),
+    ((96, 96, 98, 100), 2, 32, "measure"),  # 90.3e6 links of 48 bytes
+])
+def test_attempts_in_blocks_over_4_gib(hb, L, nlat, precision, kind):
+    """Link offsets of 64 bits with two attempts (one wave per tile): sampled
+    links after one sweep against the oracle, computed link by link; the fused
+    plaquette against su3_plaquette.  Bounds as for one attempt at this coupling."""
+    import os
+    import sys
+
+    import torch
+
+    sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+    from cone import FirstSweepCone, sample_lids
+    from oracle import su3ref
+
+    link_bytes, _ = hb.su3_footprint(hb.make_params(L, nlat=nlat, precision=precision))
+    assert link_bytes // 8 > 1 << 32
+    if torch.cuda.mem_get_info()[0] < link_bytes + (2 << 30):
+        pytest.skip("not enough device memory")
+    _say(f"attempts, 64-bit offsets L={L} nlat={nlat} precision={precision} {kind}")
+    lat = hb.Lattice(L, nlat=nlat, precision=precision, nhit=2, seed=1)
+    lat.start(True)
+    if kind == "betas":
+        lat.sweep_betas(1, 5.7, 5.7)  # equal couplings: the single-coupling chain
+    else:
+        fused = lat.sweep_measure(1, 5.7)[0]
+        assert np.abs(fused - lat.plaquette()).max() <= (1e-13 if precision == 64 else 1e-7)
+    lids = sample_lids(4 * lat.V * nlat, 18)
+    got = lat.link_sample(lids)
+    cone = FirstSweepCone(L, nlat=nlat, seed=1, beta=5.7, nhit=2)
+    dev = np.array([np.abs(su3ref.to_complex(got[k]) - cone.value(l)).max() for k, l in enumerate(lids)])
+    if precision == 64:
+        assert dev.max() < 1e-12
+    else:
+        assert np.median(dev) < 1e-5 and np.mean(dev < 1e-4) > 0.9
