@@ -204,9 +204,18 @@ int plaq_blocks(const Geom &g)
 // takes FP64 lattices with enough columns for two waves per SIMD
 // (kPlaqWalkThreads) in chunks of at least kPlaqWalkMinSteps sites: 32^4 161 us
 // against 185 us by tiles, 64^4 1.93 against 3.6 ms.  Smaller ones, which fit
-// the memory-side cache, are faster by tiles (24^4, 1.3 waves per SIMD: 66
-// against 72 us), and so is FP32 (32^4 106 us, 64^4 1.49 ms).
-constexpr long long kPlaqWalkThreads = 131072, kPlaqWalkMinSteps = 4;
+// the memory-side cache, are faster by tiles, as the last workgroups of the walk
+// leave half the CUs idle, and so is FP32 (32^4 106 us, 64^4 1.49 ms).  But from
+// one wave per SIMD on (kPlaqWalkMin) the walk keeps, us per call by walk / by tiles:
+//   one workgroup on every CU (65536 threads): 32^3 x 8 57 / 61, 64 x 64 x 16 x 4 58 / 68,
+//     2 x 32^3 x 6 71 / 90, 8^3 x 512 60 / 64 (12^3 x 160, 276 workgroups: 72 / 62);
+//   whole columns: 64 x 64 x 20 x 4 72 / 74, 48^3 x 6 105 / 129 (64 x 64 x 18 x 4, 288 workgroups:
+//     71 / 68; 24^4 in six chunks 73 / 66);
+//   on two layers up to four chunks with 1.5 workgroups per CU: 2 x 24^3 x 16 84 / 89,
+//     2 x 32 x 32 x 16 x 12 78 / 82 (2 x 20^3 x 24 in six chunks 82 / 78; one layer, 32^3 x 12 74 / 74);
+//   more than kPlaqBlocksMax tiles per layer, of which a workgroup then takes two: 26^3 x 30 98 / 115,
+//     6 x 10 x 14 x 626 117 / 139 (600: 109 / 97).
+constexpr long long kPlaqWalkThreads = 131072, kPlaqWalkMin = 65536, kPlaqWalkMinSteps = 4;
 
 int plaq_walk_chunks(const Geom &g, int precision)
 {
@@ -214,7 +223,13 @@ int plaq_walk_chunks(const Geom &g, int precision)
     const long long cols = (long long)g.nlat * g.L[0] * g.L[1] * g.L[2];
     long long nch = ceil_div(kPlaqWalkThreads, cols);
     if (nch > g.L[3] / kPlaqWalkMinSteps) nch = g.L[3] / kPlaqWalkMinSteps;
-    return nch >= 1 && cols * nch >= kPlaqWalkThreads ? (int)nch : 0;
+    const long long threads = cols * nch;
+    if (nch < 1 || threads < kPlaqWalkMin) return 0;
+    const bool walks = threads >= kPlaqWalkThreads || threads == kPlaqWalkMin ||
+                       (nch == 1 && 4 * threads >= 5 * kPlaqWalkMin) ||
+                       (g.nlat == 2 && nch <= 4 && 2 * threads >= 3 * kPlaqWalkMin) ||
+                       ceil_div(g.Vh, 64) > kPlaqBlocksMax;
+    return walks ? (int)nch : 0;
 }
 
 int plaq_walk_blocks(const Geom &g, int nch)

@@ -48,7 +48,7 @@ int plaq_blocks(const Geom &g);
 // workgroups per layer of the plaquette by tiles (its partials: meas_offset)
 int plaq_tile_blocks(const Geom &g);
 // Chunks of x3 per column of the plaquette walk (k_plaq_walk) for links of
-// the given precision, or 0 where the per-site kernels run instead (FP32, and
+// the given precision, or 0 where the plaquette goes by tiles instead (FP32, and
 // lattices too small to walk).
 int plaq_walk_chunks(const Geom &g, int precision);
 // workgroups per layer of the plaquette walk with nch chunks (<= plaq_blocks)
