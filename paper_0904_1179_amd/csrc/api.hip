@@ -389,8 +389,7 @@ su3_status su3_plaquette_noalloc(const su3_params *p, const void *d_links, size_
         return fail(SU3_ENOSPC, "link buffer has " + std::to_string(link_bytes) + " bytes, needs " +
                                     std::to_string(link_bytes_of(p, g)));
     // partial sums, then the 4 sums (the same layout as a context's scratch from kOffSums on)
-    const size_t partial_bytes = 2 * sizeof(double) * (size_t)p->nlat * (size_t)plaq_tile_blocks(g);
-    const size_t need = 256 + partial_bytes;
+    const size_t need = 256 + plaq_partial_bytes(g, p->precision);
     if (need > kNoallocScratchBytes)
         return fail(SU3_EINVAL, "lattice needs " + std::to_string(need) + " bytes of workspace, more than the " +
                                     std::to_string(kNoallocScratchBytes) + " of su3_plaquette_noalloc");

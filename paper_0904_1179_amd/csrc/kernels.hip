@@ -583,31 +583,27 @@ static void plaq_launch(const store_t<R> *links, const Geom &g, int nblk, int tp
 hipError_t launch_plaquette(int precision, const void *links, const Geom &g, double *partials, double *sums,
                             hipStream_t s, double *mean)
 {
-    const int nch = plaq_walk_chunks(g, precision);
+    const int nch = plaq_walk_chunks(g, precision), nblk = plaq_launch_blocks(g, precision);
+    const double tol = unitarity_tol(precision);
     if (nch > 0) {
         // FP64 lattices with enough columns: the x3 walk
-        const int nblk = plaq_walk_blocks(g, nch);
         const dim3 grid(nblk, g.nlat);
         const long long tiles = ((long long)g.L[0] * g.L[1] * g.L[2] * nch + kPlaqWalkBlock - 1) / kPlaqWalkBlock;
         const int tpb = (int)((tiles + nblk - 1) / nblk);
-        const double tol = unitarity_tol(precision);
         if (g.nlat == 2)
             k_plaq_walk<double, true><<<grid, kPlaqWalkBlock, 0, s>>>((const double2 *)links, g, nch, tpb, tol,
                                                                       partials);
         else
             k_plaq_walk<double, false><<<grid, kPlaqWalkBlock, 0, s>>>((const double2 *)links, g, nch, tpb, tol,
                                                                        partials);
-        k_plaq_final<<<1, kSumBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
-        return hipGetLastError();
+    } else {
+        const long long tiles = ((long long)g.Vh + 63) / 64;
+        const int tpb = (int)((tiles + nblk - 1) / nblk);
+        if (precision == 64)
+            plaq_launch<double>((const double2 *)links, g, nblk, tpb, tol, pass_big(g, 64), partials, s);
+        else
+            plaq_launch<float>((const float2 *)links, g, nblk, tpb, tol, pass_big(g, 32), partials, s);
     }
-    const int nblk = plaq_tile_blocks(g);
-    const long long tiles = ((long long)g.Vh + 63) / 64;
-    const int tpb = (int)((tiles + nblk - 1) / nblk);
-    const double tol = unitarity_tol(precision);
-    if (precision == 64)
-        plaq_launch<double>((const double2 *)links, g, nblk, tpb, tol, pass_big(g, 64), partials, s);
-    else
-        plaq_launch<float>((const float2 *)links, g, nblk, tpb, tol, pass_big(g, 32), partials, s);
     k_plaq_final<<<1, kSumBlock, 0, s>>>(partials, nblk, g.nlat, sums, mean, 36.0 * (double)g.Vh);
     return hipGetLastError();
 }

@@ -82,8 +82,8 @@ inline hipError_t launch_batch(int precision, const BatchArgs &b)
 
 hipError_t launch_start(int precision, void *links, const Geom &g, int hot, uint64_t seed, hipStream_t s);
 // Plaquette sums of the whole lattice into sums[0..3] (total, per layer,
-// number of links failing the unitarity check); partials: 2 * nlat *
-// plaq_tile_blocks(g) doubles.  With `mean` non-null also the normalised values
+// number of links failing the unitarity check); partials: plaq_partial_bytes(g,
+// precision) bytes.  With `mean` non-null also the normalised values
 // mean[0..nlat] and the failing-link count mean[1 + nlat], on the device.
 hipError_t launch_plaquette(int precision, const void *links, const Geom &g, double *partials, double *sums,
                             hipStream_t s, double *mean = nullptr);

@@ -237,6 +237,17 @@ int plaq_walk_blocks(const Geom &g, int nch)
     return even_blocks(ceil_div((long long)g.L[0] * g.L[1] * g.L[2] * nch, kPlaqWalkBlock), plaq_blocks(g));
 }
 
+int plaq_launch_blocks(const Geom &g, int precision)
+{
+    const int nch = plaq_walk_chunks(g, precision);
+    return nch > 0 ? plaq_walk_blocks(g, nch) : plaq_tile_blocks(g);
+}
+
+size_t plaq_partial_bytes(const Geom &g, int precision)
+{
+    return 2 * sizeof(double) * (size_t)g.nlat * (size_t)plaq_launch_blocks(g, precision);
+}
+
 int meas_blocks(const Geom &g, int lanes) { return pass_blocks(g, pass_links_per_block(g, lanes)); }
 
 int polyakov_blocks(const Geom &g) { return (int)ceil_div((long long)g.L[0] * g.L[1] * g.L[2], kBlock); }

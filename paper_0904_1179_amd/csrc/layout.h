@@ -53,6 +53,10 @@ int plaq_tile_blocks(const Geom &g);
 int plaq_walk_chunks(const Geom &g, int precision);
 // workgroups per layer of the plaquette walk with nch chunks (<= plaq_blocks)
 int plaq_walk_blocks(const Geom &g, int nch);
+// workgroups per layer of the plaquette of links of the given precision
+int plaq_launch_blocks(const Geom &g, int precision);
+// bytes of its partials
+size_t plaq_partial_bytes(const Geom &g, int precision);
 // workgroups of a measured pass of su3_sweep_measure
 int meas_blocks(const Geom &g, int lanes = 1);
 // Polyakov loops: workgroups per layer
