@@ -235,13 +235,15 @@ su3_status su3_gauge_transform(su3_ctx *c, uint64_t gseed);
 su3_status su3_profile(su3_ctx *c, int32_t enable);
 su3_status su3_profile_read(su3_ctx *c, double *total_ms, uint64_t *passes);
 
-/* Lanes per link of the heat-bath passes: a setting from when small passes
- * shared the work of one link between 2 or 4 lanes.  Every pass now runs three
- * waves per 64 links, one per staple direction, at any size; the setting has no
- * effect on it and none on the results.  lanes = 0 (the default) lets
- * su3_get_lanes_per_link report 4 (1-hit passes of up to 8192 links), 2 (up to
- * 32768) or 1; lanes = 1, 2 or 4 is reported back (2 and 4 need nhit = 1, else
- * SU3_EINVAL). */
+/* Work per link shared between lanes.  A pass runs six waves per 64 links where
+ * few tiles leave the GPU waiting for the chain of one update, else three (with
+ * several attempts per subgroup also one); by default (lanes = 0) the library
+ * chooses by size.  lanes = 1 asks for three waves instead of six, lanes = 2 or
+ * 4 for six at any size (1-hit only, else SU3_EINVAL; blocks of 4 GiB and more
+ * keep three).  The result does not depend on it: every variant adds in the
+ * same order and gives the same bits.  su3_get_lanes_per_link returns the
+ * count set, and with lanes = 0 the nominal one of the pass size: 4 (1-hit
+ * passes of up to 8192 links), 2 (up to 32768) or 1. */
 su3_status su3_set_lanes_per_link(su3_ctx *c, int32_t lanes);
 su3_status su3_get_lanes_per_link(su3_ctx *c, int32_t *lanes);
 

@@ -30,7 +30,7 @@ struct su3_ctx {
     bool started;
     uint64_t sweep_index;  // index of the next sweep (keys the random numbers)
     uint64_t sweeps_done;  // since the last start
-    int lanes_requested;   // lanes per link of the passes: 0 = by pass size (lanes_per_link)
+    int lanes_requested;   // su3_set_lanes_per_link: 0 = waves per tile by pass size (pass_six_waves)
     // profiling
     bool profile;
     std::vector<hipEvent_t> ev;  // pairs (start, stop)
@@ -169,7 +169,7 @@ su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nul
     a.twob = betas != nullptr;
     a.big = pass_big(c->g, c->p.precision);
     const long long tiles = pass_blocks(c->g, kPassBlock);
-    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, tiles);
+    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, tiles, c->lanes_requested);
     a.one_lane = pass_one_lane(c->p.precision, c->p.nhit, std::min(a.beta0, a.beta1), meas != nullptr, a.twob, tiles);
     a.seed = c->p.seed;
     a.nhit = c->p.nhit;

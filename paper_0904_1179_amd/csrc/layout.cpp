@@ -121,8 +121,8 @@ size_t link_bytes_of(const su3_params *p, const Geom &g)
     return (size_t)8 * kEntries * (size_t)g.stride * (p->precision == 64 ? 16u : 8u);
 }
 
-// Every pass runs three waves per 64 links whatever this count; it stays a
-// setting of the interface.
+// The sizes at which small passes shared one link's work between 2 or 4 lanes,
+// kept for what su3_get_lanes_per_link reports; pass_six_waves has its own.
 constexpr long long kLanes4Max = 8192, kLanes2Max = 32768;
 
 int lanes_per_link(const Geom &g, int nhit, int requested)
@@ -148,8 +148,9 @@ bool pass_big(const Geom &g, int precision)
 //   FP32          768 tiles 8.3 / 8.6, 1024 9.6 / 9.5;
 //   FP32, 3 hits  512 tiles 9.8 / 11.0, 576 11.6 / 11.4 (six waves make every
 //                 second draw, three only the likely ones).
-bool pass_six_waves(int precision, bool hit1, long long tiles)
+bool pass_six_waves(int precision, bool hit1, long long tiles, int requested)
 {
+    if (requested > 0) return requested > 1;
     return tiles <= (precision == 64 ? 256 : hit1 ? 768 : 512);
 }
 

@@ -28,18 +28,18 @@ size_t link_bytes_of(const su3_params *p, const Geom &g);
 inline double unitarity_tol(int precision) { return precision == 64 ? 1e-10 : 1e-5; }
 
 // The count that su3_get_lanes_per_link reports: `requested` if 1, 2 or 4, and
-// for 0 one by the number of links per pass.  The passes do not depend on it.
+// for 0 one by the number of links per pass.
 int lanes_per_link(const Geom &g, int nhit, int requested);
 // Whether a (direction, parity) block reaches 4 GiB, so that link offsets need
 // 64 bits.
 bool pass_big(const Geom &g, int precision);
 // Whether a pass of that many tiles of 64 links gives the random draws to three
-// waves of their own.
-bool pass_six_waves(int precision, bool hit1, long long tiles);
+// waves of their own; `requested` lanes per link of 1 say no, 2 and 4 yes.
+bool pass_six_waves(int precision, bool hit1, long long tiles, int requested = 0);
 // Whether a pass with several attempts runs one wave per tile; beta: the
 // smaller coupling of the layers, twob: each has its own.
 bool pass_one_lane(int precision, int nhit, double beta, bool measured, bool twob, long long tiles);
-// Links per workgroup of a pass (64, whatever the lanes).
+// Links per workgroup of a pass: 64, whatever the lanes and waves.
 int pass_links_per_block(const Geom &g, int lanes);
 // workgroups covering the nlat * Vh links of one pass, nb links each
 int pass_blocks(const Geom &g, int nb);

@@ -108,9 +108,49 @@ static void steps(const su3_params &p)
                         }
 }
 
+// waves per tile of 64 links: six, three or one
+static void waves()
+{
+    CHECK(pass_six_waves(64, true, 256) && !pass_six_waves(64, true, 257), "FP64");
+    CHECK(pass_six_waves(32, true, 768) && !pass_six_waves(32, true, 769), "FP32");
+    CHECK(pass_six_waves(32, false, 512) && !pass_six_waves(32, false, 513), "FP32, several attempts");
+    // asked for: three waves on the smallest lattice, six on a large one
+    for (int prec : {64, 32}) {
+        CHECK(!pass_six_waves(prec, true, 1, 1) && !pass_six_waves(prec, false, 1, 1), "lanes = 1");
+        CHECK(pass_six_waves(prec, true, 8192, 2) && pass_six_waves(prec, true, 8192, 4), "lanes = 2, 4");
+    }
+    const struct {
+        int prec, nhit;
+        double beta;
+        bool measured, twob;
+        int tiles;
+        bool one;
+    } c[] = {
+        {64, 1, 0.5, false, false, 1000000, false}, {64, 3, 0.5, false, false, 3, false},  {64, 64, 0.2, false, false, 1, true},
+        {64, 17, 2.0, false, false, 32, true},      {64, 17, 5.7, false, false, 32, false}, {64, 3, 4.2, false, false, 284, false},
+        {64, 7, 0.5, true, false, 284, true},       {32, 7, 0.5, true, false, 284, false},  {64, 2, 0.5, false, false, 1088, true},
+        {64, 3, 2.0, true, false, 1088, true},      {64, 3, 5.5, false, true, 324, false},  {64, 2, 5.5, false, true, 1088, true},
+        {32, 2, 0.5, false, false, 1088, false},    {32, 2, 0.5, false, false, 2176, true}, {32, 3, 5.7, false, false, 32767, false},
+        {32, 3, 5.7, false, false, 32768, true},    {64, 3, 5.7, true, false, 8192, true},  {64, 3, 5.7, false, false, 8192, false},
+        {64, 3, 5.7, false, false, 16384, true},    {64, 9, 0.4, false, false, 600, true},  {32, 9, 0.4, false, false, 600, true},
+    };
+    for (const auto &k : c)
+        CHECK(pass_one_lane(k.prec, k.nhit, k.beta, k.measured, k.twob, k.tiles) == k.one, "FP%d, %d attempts, beta %g, %d tiles",
+              k.prec, k.nhit, k.beta, k.tiles);
+    // 64-bit offsets and several attempts: one wave per tile by size alone
+    for (const su3_params &p : {params(96, 96, 98, 100, 1, 64, 2), params(128, 128, 112, 100, 1, 32, 2), params(96, 96, 98, 100, 2, 32, 2)}) {
+        const Geom g = make_geom(&p);
+        CHECK(pass_big(g, p.precision), "blocks over 4 GiB");
+        CHECK(pass_one_lane(p.precision, p.nhit, 1e9, false, false, pass_blocks(g, kPassBlock)), "one wave per tile");
+    }
+    const su3_params below = params(96, 96, 96, 96);
+    CHECK(!pass_big(make_geom(&below), 64), "96^4");
+}
+
 int main()
 {
     walks();
+    waves();
     scratch();
     for (const su3_params &p : {params(2, 2, 2, 2), params(4, 6, 2, 8), params(10, 2, 6, 4, 2), params(6, 8, 10, 2)}) steps(p);
     std::printf("%d failures\n", fails);
