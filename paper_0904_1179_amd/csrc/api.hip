@@ -169,7 +169,7 @@ su3_status enqueue_sweeps(su3_ctx *c, int32_t n, double beta, double *meas = nul
     a.twob = betas != nullptr;
     a.big = pass_big(c->g, c->p.precision);
     const long long tiles = pass_blocks(c->g, kPassBlock);
-    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1, tiles, c->lanes_requested);
+    a.six_waves = pass_six_waves(c->p.precision, c->p.nhit == 1 && !a.twob, tiles, c->lanes_requested);
     a.one_lane = pass_one_lane(c->p.precision, c->p.nhit, std::min(a.beta0, a.beta1), meas != nullptr, a.twob, tiles);
     a.seed = c->p.seed;
     a.nhit = c->p.nhit;

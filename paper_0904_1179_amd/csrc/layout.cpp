@@ -141,17 +141,22 @@ bool pass_big(const Geom &g, int precision)
 // Six waves per tile instead of three take the draws out of the chain that a
 // pass with few tiles waits for; with more tiles than run at once only the
 // number of instructions and the waves per SIMD count, and six waves hold
-// their registers until the slowest ends.  us per pass, six against three waves:
-//   FP64          256 tiles 6.8 / 7.4, 320 9.7 / 9.1 (a second workgroup of six
-//                 waves of 152 registers does not fit a CU beside the first);
-//   FP64, 3 hits  256 tiles 10.5 / 11.5, 320 13.1 / 13.0;
-//   FP32          768 tiles 8.3 / 8.6, 1024 9.6 / 9.5;
-//   FP32, 3 hits  512 tiles 9.8 / 11.0, 576 11.6 / 11.4 (six waves make every
-//                 second draw, three only the likely ones).
-bool pass_six_waves(int precision, bool hit1, long long tiles, int requested)
+// their registers until the slowest ends.  us per pass, six against three waves
+// (measured: of a sweep whose odd passes of mu = 1, 2, 3 measure):
+//   FP64           256 tiles 6.8 / 7.5, 320 9.9 / 9.2 (a second workgroup of six
+//                  waves of 152 registers does not fit a CU beside the first);
+//   FP64, 3 hits   256 tiles 10.5 / 11.5, 320 13.1 / 13.0;
+//   FP64 measured  256 tiles 7.7 / 8.3, 320 10.9 / 10.1; two layers 8.5 / 9.1, 12.5 / 10.8;
+//   FP64 couplings 256 tiles 7.3 / 8.0, 320 10.7 / 9.6;
+//   FP32           768 tiles 8.4 / 8.7, 896 9.4 / 9.3;
+//   FP32, 3 hits   512 tiles 9.8 / 11.0, 576 11.6 / 11.4 (six waves make every
+//                  second draw, three only the likely ones);
+//   FP32 measured  768 tiles 9.5 / 9.7, 896 10.7 / 10.4; two layers 10.9 / 10.9, 12.5 / 12.0;
+//   FP32 couplings 512 tiles 7.8 / 8.6, 640 10.1 / 9.1 (100 registers: four waves per SIMD).
+bool pass_six_waves(int precision, bool plain, long long tiles, int requested)
 {
     if (requested > 0) return requested > 1;
-    return tiles <= (precision == 64 ? 256 : hit1 ? 768 : 512);
+    return tiles <= (precision == 64 ? 256 : plain ? 768 : 512);
 }
 
 // Several attempts, one wave per tile instead of three (or six): it has all its

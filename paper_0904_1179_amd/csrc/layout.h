@@ -34,8 +34,9 @@ int lanes_per_link(const Geom &g, int nhit, int requested);
 // 64 bits.
 bool pass_big(const Geom &g, int precision);
 // Whether a pass of that many tiles of 64 links gives the random draws to three
-// waves of their own; `requested` lanes per link of 1 say no, 2 and 4 yes.
-bool pass_six_waves(int precision, bool hit1, long long tiles, int requested = 0);
+// waves of their own; plain: one attempt and one coupling; `requested` lanes per
+// link of 1 say no, 2 and 4 yes.
+bool pass_six_waves(int precision, bool plain, long long tiles, int requested = 0);
 // Whether a pass with several attempts runs one wave per tile; beta: the
 // smaller coupling of the layers, twob: each has its own.
 bool pass_one_lane(int precision, int nhit, double beta, bool measured, bool twob, long long tiles);

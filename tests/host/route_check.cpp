@@ -113,7 +113,7 @@ static void waves()
 {
     CHECK(pass_six_waves(64, true, 256) && !pass_six_waves(64, true, 257), "FP64");
     CHECK(pass_six_waves(32, true, 768) && !pass_six_waves(32, true, 769), "FP32");
-    CHECK(pass_six_waves(32, false, 512) && !pass_six_waves(32, false, 513), "FP32, several attempts");
+    CHECK(pass_six_waves(32, false, 512) && !pass_six_waves(32, false, 513), "FP32, several attempts or couplings");
     // asked for: three waves on the smallest lattice, six on a large one
     for (int prec : {64, 32}) {
         CHECK(!pass_six_waves(prec, true, 1, 1) && !pass_six_waves(prec, false, 1, 1), "lanes = 1");
