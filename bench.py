@@ -59,7 +59,7 @@ PROFILE_DIR = os.path.join(ROOT, "profiles")
 # what the pass kernel's counters depend on: its code, its launch shape, the
 # pass order the host picks and the compiler flags
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_0904_1179_amd", "csrc", f)
-                  for f in ("pass.h", "pass_kernels.h", "pass_f64.hip", "pass_f32.hip", "kernels.hip", "device.h",
+                  for f in ("pass.h", "pass_kernels.h", "pass_f64.hip", "pass_f32.hip", "pass_lane.h", "kernels.hip", "device.h",
                             "geom.h", "launch.h", "layout.cpp", "api.hip")] + \
                  [os.path.join(ROOT, "paper_0904_1179_amd", "build.py")]
 

@@ -21,8 +21,6 @@ template <typename R> struct Cx {
     R re, im;
 };
 
-template <typename R> __device__ __forceinline__ Cx<R> cx(R re, R im) { return Cx<R>{re, im}; }
-
 // a * b
 template <typename R> __device__ __forceinline__ Cx<R> cmul(Cx<R> a, Cx<R> b)
 {
@@ -114,11 +112,6 @@ template <typename R> __device__ __forceinline__ M3<R> mul_nn(const M3<R> &A, co
     return C;
 }
 
-template <typename R> __device__ __forceinline__ R retrace(const M3<R> &A)
-{
-    return A.e[0][0].re + A.e[1][1].re + A.e[2][2].re;
-}
-
 // ---------------------------------------------------------------------------
 // FP64 elementary functions on the argument ranges of the heat bath.  The
 // general library versions handle every input (signs, infinities, huge
@@ -127,13 +120,12 @@ template <typename R> __device__ __forceinline__ R retrace(const M3<R> &A)
 // with exact coefficients, accurate to about an ulp over those ranges.  The
 // passes issue one vector instruction per 4 cycles at best, whatever it is, so
 // the count is what matters: range reduction on the integer the uniform is
-// made of, and the hardware's reciprocal and reciprocal square root with just
-// the correction that gives the library's result.
+// made of, and the hardware's reciprocal and reciprocal square root with as much
+// correction as an ulp takes.
 // ---------------------------------------------------------------------------
 
 // n / d for |n| < d, d in [1.7, 2.5]: the hardware reciprocal r0 (2^-24), e =
-// 1 - d r0, r = r0 (1 + e + e^2) up to e^3, and one residual correction of n r:
-// the rounded quotient (on 5e8 arguments of log_unit it never differed).
+// 1 - d r0, r = r0 (1 + e + e^2) up to e^3, and one residual correction of n r.
 // The general division's scaling and special cases cannot occur here.
 __device__ __forceinline__ double div_mid(double n, double d)
 {
@@ -506,11 +498,6 @@ __device__ __forceinline__ int order_site(const Geom &g, int par, int v, int x[4
     x[0] = 2 * x0h + ((par + x[1] + x[2] + x[3]) & 1);
     return x0h + l0h * (x[1] + g.L[1] * (x[2] + g.L[2] * x[3]));
 }
-__device__ __forceinline__ int order_index(const Geom &g, int v)
-{
-    int x[4];
-    return order_site(g, 0, v, x);
-}
 
 // Link storage.  A link is stored as its rows 0 and 1, the six complex
 // entries e = 3 row + col < 6; row 2 of an SU(3) matrix is conj(row 0 x row 1)
@@ -584,21 +571,6 @@ template <typename R> __device__ __forceinline__ M3<R> mul_nd_su3(const M3<R> &A
 #pragma unroll
             for (int k = 0; k < 3; ++k) t = cmadd_nc(t, A.e[a][k], B.e[b][k]);
             C.e[a][b] = t;
-        }
-    rebuild_row2(C);
-    return C;
-}
-// A^+ B
-template <typename R> __device__ __forceinline__ M3<R> mul_dn_su3(const M3<R> &A, const M3<R> &B)
-{
-    M3<R> C;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            Cx<R> t = cmul_cn(A.e[0][a], B.e[0][b]);
-            t = cmadd_cn(t, A.e[1][a], B.e[1][b]);
-            C.e[a][b] = cmadd_cn(t, A.e[2][a], B.e[2][b]);
         }
     rebuild_row2(C);
     return C;

@@ -15,8 +15,8 @@ namespace su3hb {
 constexpr int kTile = 16;
 constexpr int kEntries = 6;
 
-constexpr int kBlock = 256;          // threads per workgroup (4 waves of 64)
-constexpr int kPassBlock = 64;       // threads per workgroup of the one-wave pass kernels
+constexpr int kBlock = 256;          // threads per workgroup of the kernels around the passes (4 waves of 64)
+constexpr int kPassBlock = 64;       // links per workgroup of a pass (its tile)
 constexpr int kPlaqBlocksMax = 4096; // workgroups per layer of the plaquette reduction
 constexpr int kPlaqWalkBlock = 256;  // threads per workgroup of the plaquette walk
 constexpr int kCounterSlots = 4096;  // heat-bath counter slots (pairs of u64: attempts, accepts)

@@ -406,12 +406,14 @@ __device__ __forceinline__ double plaq_column(const store_t<R> *__restrict__ lin
     return s;
 }
 
-// Plaquette of large FP64 lattices by walking x3: grid (nblk, nlat),
-// workgroup b (XCD-remapped) takes the threads [b T, (b+1) T) of the column
-// order (walk_column), T = tiles_per_block kPlaqWalkBlock.  Output as k_plaq.
-// Each link comes from HBM once and its reuse along x3 from registers: a call
-// at 32^4 (4 chunks of 8, two waves per SIMD) takes 161 us against 185 us by
-// tiles, at 64^4 1.93 against 3.6 ms.
+// Plaquette of FP64 lattices by walking x3 (plaq_walk_chunks says which): grid
+// (nblk, nlat), workgroup b (XCD-remapped) takes the threads [b T, (b+1) T) of
+// the column order (walk_column), T = tiles_per_block kPlaqWalkBlock.  Output as
+// k_plaq.  The reuse of a link along x3 comes from registers; its reuse by the
+// three backward neighbours in the slab comes from L2 as far as that holds the
+// sites in flight (32^4: 2.4 times the stored bytes past L2).  A call at 32^4
+// (4 chunks of 8, two waves per SIMD) takes 161 us against 185 us by tiles, at
+// 64^4 1.97 against 3.6 ms.
 template <typename R, bool DLT>
 __global__ __launch_bounds__(kPlaqWalkBlock, 2) void k_plaq_walk(const store_t<R> *__restrict__ links, const Geom g,
                                                                  const int nch, const int tiles_per_block,

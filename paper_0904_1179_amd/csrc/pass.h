@@ -4,8 +4,9 @@
 //
 // What bounds a pass.  A SIMD issues one vector instruction per 4 cycles, FP64,
 // FP32 and 64-bit integer alike (moves and bit operations in half of that when
-// four waves share it), and one wave alone only one per 8 cycles.  An update
-// is about 3000 vector instructions for 864 (FP64) or 432 (FP32) bytes, so a
+// four waves share it), and one wave alone only one per 8 cycles.  A tile of 64
+// updates is about 3500 vector instructions in all (three waves of 1150 to 1170
+// each, 32^4) for 864 (FP64) or 432 (FP32) bytes per update, so a
 // pass needs at least two, better three or four waves per SIMD that are ready
 // to issue, and every instruction counts.
 #pragma once
