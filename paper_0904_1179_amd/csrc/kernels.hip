@@ -413,7 +413,7 @@ __device__ __forceinline__ double plaq_column(const store_t<R> *__restrict__ lin
 // three backward neighbours in the slab comes from L2 as far as that holds the
 // sites in flight (32^4: 2.4 times the stored bytes past L2).  A call at 32^4
 // (4 chunks of 8, two waves per SIMD) takes 161 us against 185 us by tiles, at
-// 64^4 1.97 against 3.6 ms.
+// 64^4 1.93 against 3.6 ms.
 template <typename R, bool DLT>
 __global__ __launch_bounds__(kPlaqWalkBlock, 2) void k_plaq_walk(const store_t<R> *__restrict__ links, const Geom g,
                                                                  const int nch, const int tiles_per_block,
